@@ -194,11 +194,11 @@ size_t rag_attn_decode_workspace_size(int32_t num_decode_seqs,
  *   num_splits  0 = automatic; else the number of KV splits per decode row
  *            (clamped to [1, min(64, max_blocks_per_seq)]).
  *            Automatic: about one unit of work per CU.  A pure decode batch
- *            (cu_seqlens_q == NULL) with fewer (row, kv head) pairs than that
- *            has the pages of all its rows, per kv head, cut into equal
- *            ranges of at least 16 pages, so that rows of different lengths
- *            still give every unit the same amount to read; otherwise every
- *            row is cut into the same number of splits.
+ *            (cu_seqlens_q == NULL) of at most 256 rows is cut on the GPU from
+ *            its rows' lengths, so that rows of different lengths still give
+ *            every CU about the same amount to read, when it has fewer (row, kv
+ *            head) pairs than CUs or a block table of at least 128 blocks;
+ *            otherwise every row is cut into the same number of splits.
  *            Pieces of a row are merged (log-sum-exp) inside the same kernel
  *            by the last one to finish.
  *   workspace, workspace_bytes  device scratch of at least
@@ -257,10 +257,12 @@ rag_status rag_attn_decode_paged_append(
  * allocate device memory: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Arguments, results and errors are those of
  * rag_attn_decode_paged (same kernels, same split policy, bit-identical
- * outputs); the split partials and arrival counters live instead in a static
- * per-device scratch array inside the library (32 MiB per GPU the library
- * runs on, held until the process ends; set up on the current device at the
- * first call, which zeroes its counters with a small kernel on `stream`).  The
+ * outputs; a batch with more (row, kv head) pairs than CUs whose balanced
+ * partials exceed the scratch is cut uniformly instead); the split partials
+ * and arrival counters live instead in a static per-device scratch array
+ * inside the library (32 MiB per GPU the library runs on, held until the
+ * process ends; set up on the current device at the first call, which zeroes
+ * its counters with a small kernel on `stream`).  The
  * call allocates and frees nothing.  It returns RAG_ERR_WORKSPACE when the
  * decode rows need more than 65,536 (row, kv head) counters or more than
  * 32 MiB - 256 KiB of partials (num_decode_seqs * num_q_heads * splits *

@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "common.h"
 #include "errors.h"
 #include "launch.h"
 #include "rag_attn.h"
@@ -84,7 +85,7 @@ constexpr int32_t kMaxGroupDecode = 16;
 constexpr int32_t kTargetUnits = 256;
 constexpr int32_t kMaxPagesPerUnit = 512;
 constexpr int32_t kMinPagesPerUnit = 16;
-constexpr int32_t kMaxSplits = 64;
+constexpr int32_t kMaxSplits = rag::kDecMaxSplits;
 
 int32_t auto_splits(int32_t num_decode, int32_t hkv, int32_t max_blocks) {
   const int64_t base = std::max<int64_t>(1, (int64_t)num_decode * hkv);
@@ -103,28 +104,42 @@ int32_t resolve_splits(int32_t num_decode, int32_t hkv, int32_t max_blocks, int3
   return std::max(1, (max_blocks + pps - 1) / pps);
 }
 
-// Balanced units per kv head for a pure decode launch with the automatic
-// policy when its (row, kv head) pairs are fewer than the units aimed at: the
-// pages of all rows are cut into equal ranges, so that rows of very different
-// lengths still give every CU the same amount to stream.  0: not used.
-int32_t balanced_units(int32_t num_decode, int32_t hkv, int32_t max_blocks, int32_t requested) {
-  // (the kernel plans over at most 4 x 64 rows, which this bound implies)
-  if (requested > 0 || num_decode <= 0 || (int64_t)num_decode * hkv >= kTargetUnits) return 0;
-  // ... and no more units than pages / kMinPagesPerUnit (what the kernel uses)
+// Balanced units of a pure decode launch with the automatic policy (units 0:
+// uniform splits instead).  The plan itself is made on the GPU from the rows'
+// lengths; here only whether it is used, the units per kv head (about one per
+// CU) and the most pieces it may cut a row into (the workspace's slots).
+//   Fewer (row, kv head) pairs than CUs: always, as uniform splits leave CUs
+//   idle or unevenly loaded.
+//   More pairs: from tables of kBalWideTable pages on, where rows can differ by
+//   enough to matter (narrower ones: one workgroup per pair, 29.0 us for 64 rows
+//   of 600 tokens against 29.8), with at most kBalManySlots pieces a row.
+constexpr int32_t kBalWideTable = 128;
+constexpr int32_t kBalManySlots = 8;
+
+struct Balanced {
+  int32_t units, slots;
+};
+
+Balanced balanced_plan(int32_t num_decode, int32_t hkv, int32_t max_blocks, int32_t requested) {
+  const Balanced none{0, 0};
+  if (requested > 0 || num_decode <= 0 || num_decode > rag::kBalMaxRows) return none;
+  const bool many = (int64_t)num_decode * hkv >= kTargetUnits;
+  if (many && max_blocks < kBalWideTable) return none;
+  // no more units than pages / kMinPagesPerUnit (what the kernel uses)
   const int64_t pages = (int64_t)num_decode * std::max(max_blocks, 1);
-  const int64_t units = std::min<int64_t>({kMaxSplits, (kTargetUnits + hkv - 1) / hkv,
-                                           pages / kMinPagesPerUnit});
-  if (units <= 1) return 0;
+  const int64_t units = std::min<int64_t>((kTargetUnits + hkv - 1) / hkv,
+                                          pages / kMinPagesPerUnit);
+  if (units <= 1) return none;
   // the kernel's page arithmetic is 32-bit
-  if (pages * (units + 1) >= ((int64_t)1 << 31)) return 0;
-  return (int32_t)units;
+  if (pages * (units + 1) >= ((int64_t)1 << 31)) return none;
+  return {(int32_t)units, (int32_t)std::min<int64_t>(units, many ? kBalManySlots : kMaxSplits)};
 }
 
 // Partial-result slots per decode row: the most pieces either policy cuts a
 // row into (this sizes the workspace whichever launch uses it).
 int32_t decode_slots(int32_t num_decode, int32_t hkv, int32_t max_blocks, int32_t requested) {
   return std::max(resolve_splits(num_decode, hkv, max_blocks, requested),
-                  balanced_units(num_decode, hkv, max_blocks, requested));
+                  balanced_plan(num_decode, hkv, max_blocks, requested).slots);
 }
 
 // Workspace: [arrival counters int32, one per (decode row, kv head)]
@@ -263,11 +278,18 @@ rag_status decode_paged_impl(const void* q, const void* k_cache, const void* v_c
   const int32_t splits =
       num_decode > 0 ? resolve_splits(num_decode, num_kv_heads, max_blocks_per_seq, num_splits)
                      : 1;
-  const int32_t slots =
-      num_decode > 0 ? decode_slots(num_decode, num_kv_heads, max_blocks_per_seq, num_splits) : 1;
-  const int32_t bal = cu_seqlens_q == nullptr
-                          ? balanced_units(num_decode, num_kv_heads, max_blocks_per_seq, num_splits)
-                          : 0;
+  // (mixed batches are cut uniformly)
+  Balanced bal = cu_seqlens_q == nullptr ? balanced_plan(num_decode, num_kv_heads,
+                                                         max_blocks_per_seq, num_splits)
+                                         : Balanced{0, 0};
+  // with the static scratch, a balanced plan whose partials do not fit gives
+  // way to the uniform splits
+  if (scratch && bal.units > 0 && (int64_t)num_decode * num_kv_heads >= kTargetUnits) {
+    const WsLayout b = workspace_layout(num_decode, num_q_heads, num_kv_heads, head_dim,
+                                        std::max(splits, bal.slots));
+    if (b.bytes - b.o_off > rag::decode_scratch_capacity()) bal = Balanced{0, 0};
+  }
+  const int32_t slots = std::max(splits, bal.slots);
   const WsLayout ws = workspace_layout(num_decode, num_q_heads, num_kv_heads, head_dim, slots);
   const size_t need = ws.bytes;
   if (!scratch && need > 0 && (workspace == nullptr || workspace_bytes < need))
@@ -281,7 +303,9 @@ rag_status decode_paged_impl(const void* q, const void* k_cache, const void* v_c
       (mixed ? rag::paged_prefill_grid(num_seqs - num_decode, num_kv_heads, group, max_seqlen_q)
              : 0) +
       std::max<int64_t>(rag::paged_decode_grid(num_decode, num_kv_heads, splits),
-                        (int64_t)bal * num_kv_heads) + 8;   // + group padding
+                        bal.units > 0 ? rag::balanced_decode_grid(num_decode, num_kv_heads,
+                                                                  bal.units)
+                                      : 0) + 8;   // + group padding
   if (grid > INT_MAX) return fail(RAG_ERR_UNSUPPORTED, "decode: batch too large for one grid");
 
   if (check_mode()) {
@@ -331,7 +355,7 @@ rag_status decode_paged_impl(const void* q, const void* k_cache, const void* v_c
   a.d = head_dim;
   a.num_splits = splits;
   a.slots = slots;
-  a.bal_units = bal;
+  a.bal_units = bal.units;
   a.scale = softmax_scale;
   a.k_new = k_new;
   a.v_new = v_new;

@@ -86,6 +86,20 @@ __device__ __forceinline__ void store_coherent(float* p, float v) {
 __device__ __forceinline__ float load_coherent(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// N consecutive floats (N = 1 or 2, naturally aligned) in one such load.
+template <int N>
+__device__ __forceinline__ void load_coherent_vec(const float* p, float (&v)[N]) {
+  static_assert(N == 1 || N == 2, "one 4- or 8-byte load");
+  if constexpr (N == 1) {
+    v[0] = load_coherent(p);
+  } else {
+    const f32x2 x = __builtin_bit_cast(
+        f32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT));
+    v[0] = x[0];
+    v[1] = x[1];
+  }
+}
 // Waits until every memory access this wave issued has completed (the
 // coherent stores above have reached the coherence point).
 __device__ __forceinline__ void wait_all_memory() {
@@ -199,7 +213,18 @@ __host__ __device__ constexpr int pf_rows_per_tile(int group, int waves) {
 constexpr int kDecThreads = 256;
 constexpr int kDecWaves = kDecThreads / kWave;
 constexpr int kDecMaxGroup = 16;           // q heads per kv head (MFMA N)
-constexpr int kDecMinPages = 16;           // fewest pages a balanced decode unit takes
+constexpr int kDecMaxSplits = 64;          // pieces of a row that a merge takes (one lane each)
+constexpr int kDecMinPages = 16;           // fewest pages a balanced decode unit is cut for
+// Balanced decode: how far above the mean load (in pages) the largest whole
+// piece may be before rows are cut across units instead.  A second piece costs
+// a unit another chain of page-id, page and merge round trips, about as long
+// as streaming this many pages.
+constexpr float kBalSlack = 48.f;
+constexpr int kBalMaxRows = 256;           // rows the balanced plan is made for
+// Balanced decode with at least one row per unit: mean pages per row from which
+// rows are cut across units (128 rows of 300-1000 tokens: 60 us whole, 77
+// across; 40 of 2k-8k: 196 whole, 130 across).
+constexpr int kBalLongRow = 96;
 
 // Per wave: the V rows of the NP pages of one step, row-major [16*NP][D + 16].
 #ifndef RAG_DEC_PAGES

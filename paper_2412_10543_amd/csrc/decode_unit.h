@@ -61,13 +61,13 @@ __device__ __forceinline__ void decode_wave(
   const int lane = threadIdx.x & 63;
   const int l16 = lane & 15, gq = lane >> 4;
 
-  // Q^T fragments: lane holds head l16, d = 32*ks + 8*gq .. +8.
+  // Q^T fragments: lane holds head l16, d = 32*ks + 8*gq .. +8.  Lanes past
+  // the group repeat its last head (their results are not used, and their
+  // scores move no maximum that the last head's do not).
   bf16x8 qf[kKs];
+  const bf16_t* ql = q + min(l16, group - 1) * D + gq * 8;
 #pragma unroll
-  for (int ks = 0; ks < kKs; ++ks) {
-    u32x4 z = {0, 0, 0, 0};
-    qf[ks] = as_bf16x8(l16 < group ? load16(q + (size_t)l16 * D + ks * 32 + gq * 8) : z);
-  }
+  for (int ks = 0; ks < kKs; ++ks) qf[ks] = as_bf16x8(load16(ql + ks * 32));
 #pragma unroll
   for (int dt = 0; dt < kDt; ++dt) oacc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -213,17 +213,28 @@ __device__ __forceinline__ void decode_wave(
 
 // Merge of the n_sp split partials of the q heads assigned to this wave (h =
 // wave, wave + W, ...), in split order.  Lane sp holds split sp's weight; the
-// partial rows are read with device-coherent loads, 16 splits at a time, each
-// lane owning D/64 consecutive output values.
+// partial rows are read with device-coherent loads, kBatch splits at a time,
+// each lane owning D/64 consecutive output values.  The first batch is
+// requested beside the log-sum-exps, not after them: a merge is a chain of
+// round trips to the coherence point (2.4 us before, 1.2 now at two splits),
+// and most rows have at most 8 splits.  (The mixed launch's eight-wave units
+// keep 16: 1714 us against 1735 with 8 on 256 rows and four pieces.)
 template <int D, int W>
 __device__ __forceinline__ void merge_splits(const DecodeOut& out, int group) {
   constexpr int kPer = D / 64;                 // 2 (D = 128) or 1 (D = 64)
-  constexpr int kBatch = 16;
+  constexpr int kBatch = W > 4 ? 16 : 8;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int h = wave; h < group; h += W) {
     const float* pl = out.part_lse + (size_t)h * out.num_splits;
     const float* po = out.part_o + (size_t)h * out.num_splits * D + lane * kPer;
     const float lse = lane < out.n_sp ? load_coherent(pl + lane) : -INFINITY;
+    float x[kBatch][kPer];
+    auto request = [&](int s0) {
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b)
+        load_coherent_vec<kPer>(po + (size_t)min(s0 + b, out.n_sp - 1) * D, x[b]);
+    };
+    request(0);
     float mx = lse;
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) mx = fmaxf(mx, wave_xor(mx, m));
@@ -235,16 +246,11 @@ __device__ __forceinline__ void merge_splits(const DecodeOut& out, int group) {
 #pragma unroll
     for (int e = 0; e < kPer; ++e) acc[e] = 0.f;
     for (int s0 = 0; s0 < out.n_sp; s0 += kBatch) {
-      float x[kBatch][kPer];
+      if (s0 > 0) request(s0);
 #pragma unroll
       for (int b = 0; b < kBatch; ++b) {
-        const int sp = s0 + b < out.n_sp ? s0 + b : s0;
-#pragma unroll
-        for (int e = 0; e < kPer; ++e) x[b][e] = load_coherent(po + (size_t)sp * D + e);
-      }
-#pragma unroll
-      for (int b = 0; b < kBatch; ++b) {
-        const float wb = __shfl(w, s0 + b < out.n_sp ? s0 + b : 0, kWave);
+        const float wb = __uint_as_float(
+            __builtin_amdgcn_readlane(__float_as_uint(w), min(s0 + b, out.n_sp - 1)));
         if (s0 + b < out.n_sp) {
 #pragma unroll
           for (int e = 0; e < kPer; ++e) acc[e] += wb * x[b][e];
@@ -286,22 +292,28 @@ __device__ __forceinline__ void decode_unit(
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int l16 = lane & 15, gq = lane >> 4;
 
-  if constexpr (kAppend) {
-    constexpr int kCh = D / 8;
-    if (wave == 0 && p_end == (kv_len + 15) >> 4 && lane < 2 * kCh) {
-      const int key = kv_len - 1;
-      const size_t dst = (size_t)table[key >> 4] * block_stride + (size_t)(key & 15) * D +
-                         (lane % kCh) * 8;
-      const bf16_t* src = (lane < kCh ? k_new : v_new) + (lane % kCh) * 8;
-      bf16_t* cache = const_cast<bf16_t*>(lane < kCh ? kc : vc);
-      *reinterpret_cast<u32x4*>(cache + dst) = load16(src);
-    }
+  // The new token's rows and their slot are requested before the pages and
+  // stored after them: nothing of the unit waits for the slot's page id.
+  constexpr int kCh = D / 8;
+  const bool store_new = kAppend && wave == 0 && p_end == (kv_len + 15) >> 4 && lane < 2 * kCh;
+  u32x4 new_row = {0, 0, 0, 0};
+  int new_page = 0;
+  if (store_new) {
+    new_page = table[(kv_len - 1) >> 4];
+    new_row = load16((lane < kCh ? k_new : v_new) + (lane % kCh) * 8);
   }
   f32x4 oacc[kDt];
   float m_used, l;
   decode_wave<D, NP, kAppend>(q, kc, vc, block_stride, table, kv_len, group,
                               p_begin + wave * NP, p_end, W * NP, scale,
                               lds + wave * L::kElemsWave, oacc, m_used, l, k_new, v_new);
+
+  if (store_new) {
+    asm volatile("" : "+v"(new_page));   // (no arithmetic on it, hence no wait, before here)
+    *reinterpret_cast<u32x4*>(const_cast<bf16_t*>(lane < kCh ? kc : vc) +
+                              (size_t)new_page * block_stride +
+                              (size_t)((kv_len - 1) & 15) * D + (lane % kCh) * 8) = new_row;
+  }
 
   // ---- merge the W waves through LDS (reusing the V slices) -------------
   // floats: O [wave][16 heads][D], then m [wave][16], then l [wave][16]

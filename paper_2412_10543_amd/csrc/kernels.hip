@@ -36,6 +36,7 @@ namespace rag {
 constexpr int kPfWgPerCu = RAG_PF_WG_PER_CU;  // workgroups per CU aimed at (load balance)
 constexpr int kPfCus = 256;
 constexpr int kPfMaxItems = 32;
+constexpr int kBalMaxChunks = kBalMaxRows / kWave;   // balanced decode: chunks of 64 rows
 
 struct TileCoord {
   int seq, kvh, h0, j;
@@ -121,6 +122,10 @@ int64_t paged_prefill_grid(int num_pieces, int hkv, int group, int max_seqlen_q)
 
 int64_t paged_decode_grid(int num_decode, int hkv, int num_splits) {
   return (int64_t)num_decode * hkv * num_splits;
+}
+
+int64_t balanced_decode_grid(int num_decode, int hkv, int bal_units) {
+  return (int64_t)hkv * (num_decode >= bal_units ? num_decode + bal_units : bal_units);
 }
 
 // Paged KV-cache write fused into the prompt prefill: the K and V rows
@@ -244,23 +249,21 @@ __device__ __forceinline__ void decode_piece(const PagedKernelArgs& a, int group
                                              size_t block_stride, int s, int kvh, int kv_len,
                                              int p_begin, int p_end, int sp, int n_sp,
                                              bf16_t* lds) {
-  const int row = a.cu_q ? a.cu_q[s] : s;
-  const int h0 = kvh * group;
+  // decode rows come first in a batch, one query row each: row s is query row s
+  const size_t head = (size_t)s * a.hq + kvh * group;
   DecodeOut out;
-  out.o = a.o + ((size_t)row * a.hq + h0) * D;
-  out.part_o = a.part_o ? a.part_o + (size_t)s * a.hq * a.slots * D + (size_t)h0 * a.slots * D
-                        : nullptr;
-  out.part_lse = a.part_lse ? a.part_lse + ((size_t)s * a.hq + h0) * a.slots : nullptr;
-  out.arrival = a.arrivals ? a.arrivals + (size_t)s * a.hkv + kvh : nullptr;
+  out.o = a.o + head * D;
+  out.part_o = a.part_o + head * a.slots * D;      // (used with more than one split only)
+  out.part_lse = a.part_lse + head * a.slots;
+  out.arrival = a.arrivals + (size_t)s * a.hkv + kvh;
   out.sp = sp;
   out.n_sp = n_sp;
   out.num_splits = a.slots;
   const size_t nrow = ((size_t)s * a.hkv + kvh) * D;
-  decode_unit<D, NP, W, kAppend>(a.q + ((size_t)row * a.hq + h0) * D,
-                                 a.kc + (size_t)kvh * 16 * D, a.vc + (size_t)kvh * 16 * D,
-                                 block_stride, a.tables + (size_t)s * a.max_blocks, kv_len, group,
-                                 p_begin, p_end, a.scale, out, lds,
-                                 kAppend ? a.k_new + nrow : nullptr,
+  decode_unit<D, NP, W, kAppend>(a.q + head * D, a.kc + (size_t)kvh * 16 * D,
+                                 a.vc + (size_t)kvh * 16 * D, block_stride,
+                                 a.tables + (size_t)s * a.max_blocks, kv_len, group, p_begin,
+                                 p_end, a.scale, out, lds, kAppend ? a.k_new + nrow : nullptr,
                                  kAppend ? a.v_new + nrow : nullptr);
 }
 
@@ -283,71 +286,160 @@ __device__ __forceinline__ void decode_block(const PagedKernelArgs& a, int u, in
                                   n_sp, lds);
 }
 
-// Balanced decode units: the pages of all rows of one kv head, laid end to
-// end (row by row), are cut into equal ranges of at least kDecMinPages pages
-// (at most bal_units of them); unit k of kv head kvh attends the pieces of the
-// rows its range covers (usually one or two), each piece split sp of the n_sp
-// units that cover its row.  Unit sizes no longer follow the rows' lengths,
-// so every CU streams the same number of pages and none is left with a long
-// tail.  The plan comes from kv_lens, loaded once (one lane per row, rows in
-// chunks of 64; fewer than 256 rows take this path) and walked with
-// wave-uniform reads.
-constexpr int kBalMaxChunks = 4;
+// Balanced decode units: a pure decode batch is cut into units from the rows'
+// actual lengths, bal_units of them per kv head where that is more than the
+// rows, else at most rows + bal_units.  Two plans, each giving row s the un
+// consecutive units from uf on:
+//   whole pieces   every row is cut on its own into equal pieces of at most
+//                  about a quota of pages, the smallest quota tried for which
+//                  the pieces fit the units: one piece per unit;
+//   crossing       the pages of all rows, laid end to end, are cut into
+//                  bal_units equal ranges; a unit attends the pieces of the
+//                  rows its range covers, one after another.
+// Crossing keeps every unit equally loaded; whole pieces spare a unit the
+// second piece's chain of page-id, page and merge round trips (4-9 us on
+// 20 rows of 600 tokens, whose launch is 13 us).  The plan is wave-parallel
+// (one lane per row, prefix sums over the lanes; kChunks chunks of 64 rows) and
+// short in code: walked row by row with integer divisions it took 3 us of that
+// launch, now 0.7.
+// Measured (7B heads, graph-replayed, before -> now): 20 rows x 600 tokens 20.3
+// -> 13.8 us, 16 x 576-1088 21.4 -> 16.6, 8 x 2.6k-10k 47.6 -> 43.3, 16 x
+// 2.6k-10k 75.1 -> 72.9, 40 x 2k-8k 195 -> 129; 255 rows x 100-900 with one kv
+// head 85 -> 18.
 
-template <int D, int NP, int W, bool kAppend>
+// Inclusive prefix sum over the wave's lanes.
+__device__ __forceinline__ int wave_scan_add(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31
+  return x;
+}
+
+template <int D, int NP, int W, bool kAppend, int kChunks>
 __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, int u, int group,
                                                       size_t block_stride, bf16_t* lds) {
   const int kvh = u % a.hkv, k = u / a.hkv;
-  if (k >= a.bal_units) return;
   const int S = a.num_decode, lane = threadIdx.x & 63, cap = a.max_blocks * 16;
-  int kl[kBalMaxChunks];
+  // per lane, rows 64 c + lane: keys, pages, first global page, units
+  int kl[kChunks], pg[kChunks], st[kChunks], un[kChunks], uf[kChunks];
 #pragma unroll
-  for (int c = 0; c < kBalMaxChunks; ++c) {
+  for (int c = 0; c < kChunks; ++c) {
     const int s = c * kWave + lane;
-    kl[c] = s < S ? min(a.kv_lens[s], cap) : 0;
+    kl[c] = min(a.kv_lens[min(s, S - 1)], cap);
+    if (s >= S) kl[c] = 0;
   }
   int total = 0;
 #pragma unroll
-  for (int c = 0; c < kBalMaxChunks; ++c)
-    for (int i = 0; i < min(kWave, S - c * kWave); ++i)
-      total += (__builtin_amdgcn_readlane(kl[c], i) + 15) >> 4;
-  // at least kDecMinPages pages per unit (short batches use fewer units)
-  const int K = max(1, min(a.bal_units, total / kDecMinPages));
-  if (k >= K) return;
-  // 32-bit arithmetic: the host takes this path only when rows x table
-  // width x units stays below 2^31
-  const uint32_t ut = (uint32_t)total, uk = (uint32_t)K;
-  const int lo = (int)((uint32_t)k * ut / uk), hi = (int)((uint32_t)(k + 1) * ut / uk);
-  // unit holding global page g: ceil((g + 1) K / total) - 1
-  auto unit_of = [&](int g) { return (int)(((uint32_t)(g + 1) * uk + ut - 1) / ut) - 1; };
-  int gs = 0;                 // first global page of the row
-  bool first_piece = true;
-  // one call site of decode_piece (rows walked in one loop, the chunk of a
-  // row picked by value): the kernel's code stays one copy of the unit
-  for (int s = 0; s < S && gs < hi; ++s) {
-    static_assert(kBalMaxChunks == 4, "row chunk select");
-    const int c = s >> 6;
-    const int klc = c == 0 ? kl[0] : c == 1 ? kl[1] : c == 2 ? kl[2] : kl[3];
-    const int kls = __builtin_amdgcn_readlane(klc, s & 63);
-    const int ps = (kls + 15) >> 4;
-    if (ps > 0 && gs + ps > lo) {
-      const int first = unit_of(gs), last = unit_of(gs + ps - 1);
-      if (!first_piece) __syncthreads();   // LDS of the previous piece fully read
-      first_piece = false;
-      decode_piece<D, NP, W, kAppend>(a, group, block_stride, s, kvh, kls,
-                                      max(lo, gs) - gs, min(hi, gs + ps) - gs, k - first,
-                                      last - first + 1, lds);
+  for (int c = 0; c < kChunks; ++c) {
+    pg[c] = (kl[c] + 15) >> 4;
+    const int incl = wave_scan_add(pg[c]);
+    st[c] = total + incl - pg[c];
+    total += __builtin_amdgcn_readlane(incl, 63);
+  }
+  // Pages per unit below which the longest row could have more pieces than the
+  // workspace has slots for (a crossing row also starts and ends inside one).
+  float q_min = (float)kDecMinPages;
+  if (a.bal_units > a.slots) {
+    int longest = pg[0];
+#pragma unroll
+    for (int c = 1; c < kChunks; ++c) longest = max(longest, pg[c]);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) longest = max(longest, __shfl_xor(longest, m, kWave));
+    longest = __builtin_amdgcn_readfirstlane(longest);
+    q_min = fmaxf(q_min, (float)longest * __builtin_amdgcn_rcpf((float)(a.slots - 2)) + 2.f);
+  }
+  // Whole pieces: quotas from the larger of q_min and the mean per unit on, up
+  // to kBalSlack pages above it.  With as many rows as units the first quota
+  // fits; long rows (by their mean) are then better cut across.  (Single
+  // precision: every wave of the launch computes the same numbers, and any
+  // piece count up to the slots is a valid cut.)
+  const bool many = S >= a.bal_units;
+  const int budget = many ? S + a.bal_units : a.bal_units;
+  const float q0 = fmaxf(q_min, (float)total * __builtin_amdgcn_rcpf((float)a.bal_units));
+  const float q_max = many && total >= kBalLongRow * S ? 0.f : q0 + kBalSlack;
+  bool whole = false;
+  for (float q = q0; q <= q_max; q = fmaxf(q * 1.25f, q + 1.f)) {
+    const float rq = __builtin_amdgcn_rcpf(q);
+    int units = 0;
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      un[c] = min((int)ceilf((float)pg[c] * rq), a.slots);
+      const int incl = wave_scan_add(un[c]);
+      uf[c] = units + incl - un[c];
+      units += __builtin_amdgcn_readlane(incl, 63);
     }
-    gs += ps;
+    if (units <= budget) {
+      whole = true;
+      break;
+    }
+  }
+  auto first_row = [&](auto pred) {          // first row with pred, or -1
+    int s = -1;
+#pragma unroll
+    for (int c = kChunks - 1; c >= 0; --c) {
+      const uint64_t at = __builtin_amdgcn_ballot_w64(pred(c));
+      if (at != 0) s = c * kWave + __builtin_ctzll(at);
+    }
+    return s;
+  };
+  auto row = [&](const int (&v)[kChunks], int r) {
+    static_assert(kChunks == 1 || kChunks == 4, "row chunk select");
+    if constexpr (kChunks == 1) {
+      return __builtin_amdgcn_readlane(v[0], r);
+    } else {                     // (values are selected: an index would put them in memory)
+      const int c = r >> 6, v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+      return __builtin_amdgcn_readlane(c == 0 ? v0 : c == 1 ? v1 : c == 2 ? v2 : v3, r & 63);
+    }
+  };
+  int lo, hi, s;                             // this unit's global pages and first row
+  if (whole) {
+    s = first_row([&](int c) { return k < uf[c] + un[c]; });
+    if (s < 0) return;
+    const int n = row(un, s), sp = k - row(uf, s), p = row(pg, s);
+    const float step = (float)p * __builtin_amdgcn_rcpf((float)n);
+    lo = row(st, s) + (int)((float)sp * step);
+    hi = row(st, s) + (sp + 1 == n ? p : (int)((float)(sp + 1) * step));
+  } else {
+    // at least q_min pages per unit; 32-bit arithmetic: the host takes this
+    // path only when rows x table width x units stays below 2^31
+    const uint32_t T = (uint32_t)total;
+    const uint32_t K =
+        max(1u, min((uint32_t)a.bal_units, (uint32_t)((float)total * __builtin_amdgcn_rcpf(q_min))));
+    if ((uint32_t)k >= K) return;
+    lo = (int)((uint32_t)k * T / K);
+    hi = (int)((uint32_t)(k + 1) * T / K);
+    // unit holding global page g: ceil((g + 1) K / T) - 1
+    auto unit_of = [&](int g) { return (int)(((uint32_t)(g + 1) * K + T - 1) / T) - 1; };
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      uf[c] = unit_of(st[c]);
+      un[c] = unit_of(st[c] + max(pg[c], 1) - 1) - uf[c] + 1;
+    }
+    s = first_row([&](int c) { return st[c] + pg[c] > lo; });
+  }
+  // one call site of decode_piece: the kernel's code stays one copy of the unit
+  for (bool first = true;; first = false) {
+    const int gs = row(st, s), ps = row(pg, s);
+    if (gs >= hi) break;
+    if (ps > 0) {
+      if (!first) __syncthreads();           // LDS of the previous piece fully read
+      decode_piece<D, NP, W, kAppend>(a, group, block_stride, s, kvh, row(kl, s),
+                                      max(lo, gs) - gs, min(hi, gs + ps) - gs, k - row(uf, s),
+                                      row(un, s), lds);
+    }
+    if (++s >= S) break;
   }
 }
 
-template <int D, bool kAppend>
+template <int D, bool kAppend, int kChunks>
 __global__ __launch_bounds__(kDecThreads, 2) void paged_decode_balanced_kernel(
     PagedKernelArgs a) {
   __shared__ __attribute__((aligned(16))) bf16_t lds[DecLds<D>::kBytes / 2];
-  decode_block_balanced<D, kDecPages, kDecWaves, kAppend>(a, blockIdx.x, a.hq / a.hkv,
-                                                          (size_t)a.hkv * 16 * D, lds);
+  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, kChunks>(
+      a, blockIdx.x, a.hq / a.hkv, (size_t)a.hkv * 16 * D, lds);
 }
 
 // Decode rows only: one four-wave workgroup per decode unit.  kAppend: each
@@ -464,7 +556,7 @@ static hipError_t launch_paged_d(const PagedArgs& a, hipStream_t stream) {
                                                 a.max_seqlen_q)
                            : 0;
   k.n_pf_blocks = (int)pf;
-  int64_t dec = k.bal_units > 0 ? (int64_t)k.bal_units * a.hkv
+  int64_t dec = k.bal_units > 0 ? balanced_decode_grid(a.num_decode, a.hkv, k.bal_units)
                                 : paged_decode_grid(a.num_decode, a.hkv, a.num_splits);
   if (pf > 0) dec = (dec + kNumXcd - 1) / kNumXcd * kNumXcd;   // whole groups of eight
   k.n_dec_groups = (int)(dec / kNumXcd);
@@ -473,12 +565,18 @@ static hipError_t launch_paged_d(const PagedArgs& a, hipStream_t stream) {
     if (pf > 0)
       hipLaunchKernelGGL(mixed_kernel<D>, dim3((unsigned)grid), dim3(64 * kPfWavesDense), 0,
                          stream, k);
-    else if (k.bal_units > 0 && a.k_new != nullptr)
-      hipLaunchKernelGGL((paged_decode_balanced_kernel<D, true>), dim3((unsigned)grid),
-                         dim3(kDecThreads), 0, stream, k);
-    else if (k.bal_units > 0)
-      hipLaunchKernelGGL((paged_decode_balanced_kernel<D, false>), dim3((unsigned)grid),
-                         dim3(kDecThreads), 0, stream, k);
+    else if (k.bal_units > 0) {
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kDecThreads), 0, stream, k);
+      };
+      const bool one = a.num_decode <= kWave;
+      if (a.k_new != nullptr)
+        one ? go(paged_decode_balanced_kernel<D, true, 1>)
+            : go(paged_decode_balanced_kernel<D, true, kBalMaxChunks>);
+      else
+        one ? go(paged_decode_balanced_kernel<D, false, 1>)
+            : go(paged_decode_balanced_kernel<D, false, kBalMaxChunks>);
+    }
     else if (a.k_new != nullptr)
       hipLaunchKernelGGL((paged_decode_kernel<D, true>), dim3((unsigned)grid), dim3(kDecThreads),
                          0, stream, k);

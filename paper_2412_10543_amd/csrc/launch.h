@@ -63,6 +63,7 @@ struct KvWriteArgs {
 int64_t prefill_grid(int num_seqs, int hkv, int group, int max_seqlen_q);
 int64_t paged_prefill_grid(int num_pieces, int hkv, int group, int max_seqlen_q);
 int64_t paged_decode_grid(int num_decode, int hkv, int num_splits);
+int64_t balanced_decode_grid(int num_decode, int hkv, int bal_units);
 
 hipError_t launch_prefill_varlen(const PrefillArgs& a, hipStream_t stream);
 hipError_t launch_paged(const PagedArgs& a, hipStream_t stream);
