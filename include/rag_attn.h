@@ -197,8 +197,9 @@ size_t rag_attn_decode_workspace_size(int32_t num_decode_seqs,
  *            (cu_seqlens_q == NULL) of at most 256 rows is cut on the GPU from
  *            its rows' lengths, so that rows of different lengths still give
  *            every CU about the same amount to read, when it has fewer (row, kv
- *            head) pairs than CUs or a block table of at least 128 blocks;
- *            otherwise every row is cut into the same number of splits.
+ *            head) pairs than CUs, or a block table of at least 128 blocks
+ *            (and the workspace that takes); otherwise every row is cut into
+ *            the same number of splits.
  *            Pieces of a row are merged (log-sum-exp) inside the same kernel
  *            by the last one to finish.
  *   workspace, workspace_bytes  device scratch of at least

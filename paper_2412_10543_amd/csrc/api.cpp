@@ -282,12 +282,16 @@ rag_status decode_paged_impl(const void* q, const void* k_cache, const void* v_c
   Balanced bal = cu_seqlens_q == nullptr ? balanced_plan(num_decode, num_kv_heads,
                                                          max_blocks_per_seq, num_splits)
                                          : Balanced{0, 0};
-  // with the static scratch, a balanced plan whose partials do not fit gives
-  // way to the uniform splits
-  if (scratch && bal.units > 0 && (int64_t)num_decode * num_kv_heads >= kTargetUnits) {
+  // With more pairs than CUs the uniform splits need less memory: they take
+  // the call where the static scratch, or the workspace given, is too small
+  // for the balanced plan.
+  if (bal.units > 0 && (int64_t)num_decode * num_kv_heads >= kTargetUnits) {
     const WsLayout b = workspace_layout(num_decode, num_q_heads, num_kv_heads, head_dim,
                                         std::max(splits, bal.slots));
-    if (b.bytes - b.o_off > rag::decode_scratch_capacity()) bal = Balanced{0, 0};
+    const bool fits =
+        scratch ? rag::decode_scratch_fits((size_t)num_decode * num_kv_heads, b.bytes - b.o_off)
+                : workspace != nullptr && workspace_bytes >= b.bytes;
+    if (!fits) bal = Balanced{0, 0};
   }
   const int32_t slots = std::max(splits, bal.slots);
   const WsLayout ws = workspace_layout(num_decode, num_q_heads, num_kv_heads, head_dim, slots);

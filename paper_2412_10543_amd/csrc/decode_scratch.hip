@@ -45,7 +45,9 @@ DeviceScratch g_dev[kMaxDevices];
 
 }  // namespace
 
-size_t decode_scratch_capacity() { return kScratchBytes - kCounterBytes; }
+bool decode_scratch_fits(size_t counters, size_t partial_bytes) {
+  return counters <= kScratchCounters && partial_bytes <= kScratchBytes - kCounterBytes;
+}
 
 rag_status decode_scratch(size_t counters, size_t partial_bytes, hipStream_t stream,
                           int** counters_out, char** partials_out) {

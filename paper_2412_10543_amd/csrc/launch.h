@@ -76,6 +76,6 @@ hipError_t launch_kv_cache_write(const KvWriteArgs& a, hipStream_t stream);
 // addresses of its zeroed counter region and of its partial-result region.
 rag_status decode_scratch(size_t counters, size_t partial_bytes, hipStream_t stream,
                           int** counters_out, char** partials_out);
-size_t decode_scratch_capacity();
+bool decode_scratch_fits(size_t counters, size_t partial_bytes);
 
 }  // namespace rag

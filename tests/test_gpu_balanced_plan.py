@@ -67,6 +67,29 @@ def test_balanced_plan(orc, rows, hq, hkv, d, kind, max_blocks):
         assert torch.equal(o.view(torch.int16), got.view(torch.int16))
 
 
+@pytest.mark.parametrize("entry", ["no workspace", "small workspace", "scratch"])
+def test_uniform_splits_where_the_plan_does_not_fit(orc, entry):
+    """More pairs than CUs: a call without the memory for the balanced plan is
+    cut uniformly (here: not at all), as one with num_splits=1."""
+    lens = _lens("spread", 40)
+    hq, hkv, d = 32, 8, 64
+    pool = paged_pool(lens, hkv, d, 970, device="cuda", max_blocks=400)
+    if entry == "scratch":                 # 256 rows x 64 heads x 8 slots: over the scratch
+        lens, hq = [17] * 256, 64
+        pool = paged_pool(lens, hkv, d, 971, device="cuda", max_blocks=200)
+    q = normal_bf16((len(lens), hq, d), 972, "cuda")
+    want = gpu_paged(q, pool, hq, hkv, d, scale_for(d), num_splits=1)
+    o = torch.full_like(q, float("nan"))
+    args = (q, pool.k_cache, pool.v_cache, o, pool.block_tables, to_dev_i32(lens), scale_for(d))
+    if entry == "scratch":
+        binding.rag_attn_decode_paged_noalloc(*args)
+    else:
+        ws = torch.zeros(256, dtype=torch.uint8, device="cuda") if entry[0] == "s" else None
+        binding.rag_attn_decode_paged(*args, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(o.view(torch.int16), want.view(torch.int16))
+
+
 @pytest.mark.parametrize("rows,hq,hkv,d,kind", [(20, 32, 8, 128, "equal"), (66, 8, 2, 64, "spread"),
                                                 (3, 8, 1, 128, "one_long")])
 def test_append_stores_after_the_pages(rows, hq, hkv, d, kind):
