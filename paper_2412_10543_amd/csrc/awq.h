@@ -20,19 +20,19 @@ struct AwqArgs {
 };
 
 struct AwqPlan {
-  bool large;                   // M > 64: LDS-staged 128 x 512 tiles
+  int md_mb;                    // awq_gemm_md_kernel: 32-row blocks per tile (0: the small one)
+  int md_nw;                    // its waves, 64 columns each
   int groups, splits, groups_per_split;
   int tiles_m, tiles_n, tiles_per_xcd;
   int sm_mb;                    // small batches: 16-row blocks (1, 2 or 4)
   int sm_nb;                    // small batches: 16-column blocks per workgroup
   int sm_a;                     // small batches: waves across the columns (NB / A blocks each)
   int64_t tiles;
-  size_t sp_bytes, part_bytes;  // large batches: group-sum pieces; split partials
-  size_t counter_bytes;         // small batches split over groups: arrival counters
-                                // (at the workspace's start)
+  size_t counter_bytes;         // arrival counters (at the workspace's start), then
+  size_t part_bytes;            // the partials of a split over the groups
 };
 
 AwqPlan awq_plan(int M, int N, int K);
-hipError_t launch_awq_gemm(const AwqArgs& a, hipStream_t stream);
+hipError_t launch_awq_gemm(const AwqArgs& a, const AwqPlan& plan, hipStream_t stream);
 
 }  // namespace rag

@@ -39,7 +39,7 @@ extern "C" {
 size_t rag_awq_workspace_size(int32_t M, int32_t N, int32_t K, int32_t group_size) {
   if (check_shape("awq workspace", M, N, K, group_size) != RAG_OK || M == 0) return 0;
   const rag::AwqPlan p = rag::awq_plan(M, N, K);
-  return p.sp_bytes + p.part_bytes + p.counter_bytes;
+  return p.counter_bytes + p.part_bytes;
 }
 
 rag_status rag_awq_pack_weights(const uint8_t* q, int32_t K, int32_t N, int32_t group_size,
@@ -82,14 +82,15 @@ rag_status rag_awq_gemm(const void* x, const int32_t* qweight, const void* scale
       !aligned(zeros, 16))
     return fail(RAG_ERR_INVALID_ARG,
                 "awq gemm: x/qweight/scales/zeros/y must be 16-byte aligned");
-  const size_t need = rag_awq_workspace_size(M, N, K, group_size);
+  const rag::AwqPlan plan = rag::awq_plan(M, N, K);
+  const size_t need = plan.counter_bytes + plan.part_bytes;
   if (!workspace || workspace_bytes < need)
     return fail(RAG_ERR_WORKSPACE, "awq gemm: workspace of %zu bytes needed, %zu given", need,
                 workspace ? workspace_bytes : (size_t)0);
   if (!aligned(workspace, 256))
     return fail(RAG_ERR_INVALID_ARG, "awq gemm: workspace must be 256-byte aligned");
   rag::AwqArgs a{x, qweight, scales, zeros, y, workspace, M, N, K};
-  const hipError_t e = rag::launch_awq_gemm(a, stream);
+  const hipError_t e = rag::launch_awq_gemm(a, plan, stream);
   if (e != hipSuccess) return fail(RAG_ERR_HIP, "awq gemm: launch failed: %s", hipGetErrorString(e));
   return rag::ok();
 }

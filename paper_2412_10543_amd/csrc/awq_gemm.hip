@@ -8,12 +8,12 @@
 // bf16 operands with one shift and one and-or.  For group g,
 //     sum_k X[m, k] W[k, n] = s[g, n] * (P[m, n] - (128 + z[g, n]) * S[g, m]),
 //     P = sum_k X[m, k] (128 + q[k, n]),   S[g, m] = sum of X[m, k] over g.
-// Large batches: a pre-pass computes S in fp32 and stores it as three bf16
-// pieces S1 + S2 + S3 = S (exact: 24 bits in 3 x 8), and the kernel folds the
-// zero-point term into the matrix cores as one more MFMA per group (A = the
+// Larger batches (awq_gemm_md_kernel): S, formed by the kernel beside its
+// products, is stored as three bf16 pieces S1 + S2 + S3 = S (exact: 24 bits in
+// 3 x 8), and the zero-point term becomes one more MFMA per group (A = the
 // pieces, B = -(128 + z), which bf16 holds exactly as bits 0xC300 | z), with a
 // running rescale of the accumulators for the scale (see there).  Small
-// batches need no pre-pass: the kernel stages its slice of X in LDS and forms
+// batches (awq_gemm_sm_kernel): the kernel stages its slice of X in LDS, forms
 // S with the matrix cores (X times a ones operand), then applies zero point
 // and scale with two fp32 FMAs per output element and group.
 //
@@ -35,41 +35,6 @@ namespace rag {
 
 constexpr int kAwqGroup = 128;
 constexpr int kAwqCus = 256;     // MI355X compute units
-
-// S[g, m] = sum over the group of X[m, k] (fp32), stored as bf16 pieces
-// [S1, S2, S3, 0, 0, 0, 0, 0] (16 bytes per (g, m)), for the large-batch
-// kernel.  16 lanes share one (g, m): lane c loads the 16-byte chunk c of the
-// group's row (consecutive lanes, consecutive chunks) and the 16 partial sums
-// are added with lane shuffles in a fixed order.
-__global__ __launch_bounds__(256) void awq_group_sums_kernel(const bf16_t* __restrict__ x,
-                                                             bf16_t* __restrict__ sp, int M,
-                                                             int K) {
-  const int groups = K / kAwqGroup;
-  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t i = tid >> 4;
-  const int c = threadIdx.x & 15;
-  if (i >= (int64_t)groups * M) return;           // whole 16-lane groups
-  const int g = (int)(i / M), m = (int)(i % M);
-  const u32x4 raw = load16(x + (size_t)m * K + (size_t)g * kAwqGroup + 8 * c);
-  const bf16x8 v = as_bf16x8(raw);
-  float acc = 0.f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) acc += (float)v[e];
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) acc += __shfl_xor(acc, o, 16);
-  if (c != 0) return;
-  const __bf16 s1 = (__bf16)acc;
-  const float r1 = acc - (float)s1;
-  const __bf16 s2 = (__bf16)r1;
-  const __bf16 s3 = (__bf16)(r1 - (float)s2);
-  u32x4 out;
-  out[0] = (uint32_t)__builtin_bit_cast(uint16_t, s1) |
-           ((uint32_t)__builtin_bit_cast(uint16_t, s2) << 16);
-  out[1] = (uint32_t)__builtin_bit_cast(uint16_t, s3);
-  out[2] = 0;
-  out[3] = 0;
-  *reinterpret_cast<u32x4*>(sp + ((size_t)g * M + m) * 8) = out;
-}
 
 // A value the compiler must keep in a VGPR (no constant folding).
 __device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
@@ -93,47 +58,6 @@ __device__ __forceinline__ bf16x8 codes_to_bf16(uint32_t w, uint32_t mask, uint3
 __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) {
   return __builtin_bit_cast(float, bits16 << 16);
 }
-
-// ---------------------------------------------------------------------------
-// Large batches: 8-wave workgroups (two waves per SIMD) own 128 x 512 tiles
-// of Y; wave w computes all 128 rows and columns 64 w .. +64 as 4 x 2 MFMA
-// blocks of 32 x 32.  Per group the workgroup stages in LDS, by direct
-// global -> LDS copies issued one group ahead into a 2-stage ring:
-//   X   128 rows x 128 k bf16, row r's 16-byte chunk c at position c ^ (r & 15)
-//       (the MFMA A reads of 16 rows then hit 16 distinct bank groups)
-//   W   512 columns x 64 bytes of codes, the 16-byte chunk j of column c at
-//       position j ^ ((c >> 2) & 3) within its 1 KB copy block
-//   SP  128 rows x 16 bytes of group-sum pieces
-//   SZ  512 bf16 scales then 512 uint8 zero points
-//
-// Scale handling.  Each scale is split exactly as s = m * 2^e with |m| in
-// [1, 2).  The power of two goes into the B operands: the magic constant's
-// exponent field becomes 134 + e, so a code turns into (128 + q) 2^e, still
-// exact in bf16 (likewise -(128 + z) 2^e for the zero-point term).  The
-// accumulators hold u = y / c with c the m of the column's last group: before
-// group g they are multiplied by c / m[g, n] (one fp32 multiply per element;
-// the ratio lies in (1/2, 2), so u never leaves the range of y), then every
-// MFMA of group g (the zero-point term and the 8 k-steps) accumulates
-// straight into them, and y = u * c at the end.  There is no separate
-// per-group accumulator, which is what lets a wave hold a 128 x 64 tile and
-// convert each code word once for 4 row blocks.  A zero scale turns the
-// column's operands to zero (mask and magic 0) and leaves c as it was.
-// ---------------------------------------------------------------------------
-namespace awq_lg {
-constexpr int kThreads = 512;
-constexpr int kBM = 128;
-constexpr int kBN = 512;
-constexpr int kStages = 2;
-constexpr int kX = kBM * kAwqGroup * 2;          // 32768
-constexpr int kW = kBN * kAwqGroup / 2;          // 32768
-constexpr int kSP = kBM * 16;                    // 2048
-constexpr int kSZ = kBN * 3;                     // 1536
-constexpr int kStage = kX + kW + kSP + kSZ;      // 69120
-constexpr int kGroupM = 8;                       // M tiles per raster group
-constexpr int kOutStride = 144;                  // bytes per row of the output transpose
-static_assert(kStage % 16 == 0, "stage alignment");
-static_assert(8 * 64 * kOutStride <= kStages * kStage, "output transpose fits");
-}  // namespace awq_lg
 
 // vmcnt <= n (n < 64), expcnt and lgkmcnt unconstrained.
 template <int n>
@@ -177,18 +101,104 @@ __device__ __forceinline__ ColScale col_scale(uint32_t sb, uint32_t z) {
   return r;
 }
 
-template <bool kSplit>
-__global__ __launch_bounds__(awq_lg::kThreads) void awq_gemm_lg_kernel(
-    const bf16_t* __restrict__ x, const uint32_t* __restrict__ qw,
-    const bf16_t* __restrict__ scales, const uint8_t* __restrict__ zeros,
-    const bf16_t* __restrict__ sp, bf16_t* __restrict__ y, float* __restrict__ part, int M,
-    int N, int K, int groups_per_split, int tiles_m, int tiles_n, int tiles_per_xcd) {
-  using namespace awq_lg;
-  __shared__ __attribute__((aligned(16))) char lds[kStages * kStage];
+// The same for scales that are all normal and below 2^121 (the caller's check,
+// plain_scale): 12 instructions instead of 30.
+__device__ __forceinline__ bool plain_scale(uint32_t sb) {
+  const uint32_t E = sb & 0x7F80u;
+  return E - 0x80u < (248u << 7) - 0x80u;
+}
+__device__ __forceinline__ ColScale col_scale_plain(uint32_t sb, uint32_t z) {
+  const uint32_t ex = (sb & 0x7F80u) + (7u << 7);       // exponent field 134 + e
+  ColScale r;
+  r.c = bf16_to_f32((sb & 0x807Fu) | 0x3F80u);
+  r.mask = 0x000F000Fu;
+  r.magic = ex | (ex << 16);
+  r.nz = 0x8000u | ex | z;
+  return r;
+}
+
+// ---------------------------------------------------------------------------
+// Larger batches: workgroups of NW waves own 32 MB x 64 NW tiles of Y; wave w
+// computes all rows and the columns 64 w .. +64 as MB x 2 MFMA blocks of 32 x 32.  The X tile of a group is shared through LDS (direct global -> LDS
+// copies one group ahead, two stages; row r's 16-byte chunk c at position
+// c ^ (r & 15), so that the A reads of 16 rows hit 16 distinct bank groups);
+// the code words, scales and zero points belong to one wave only and go from
+// memory straight into its registers, one group ahead.
+//
+// Group sums.  Each wave sums its share of the rows of the X tile (one lane per
+// row and half of a k-step, v_dot2 with ones) and stores the sums as three
+// bf16 pieces (exact) in LDS in the A layout; the zero-point MFMA of a group is
+// issued after the next barrier, when every wave's pieces are visible.
+//
+// Scale handling.  Each scale is split exactly as s = m * 2^e with |m| in
+// [1, 2).  The power of two goes into the B operands: the magic constant's
+// exponent field becomes 134 + e, so a code turns into (128 + q) 2^e, still
+// exact in bf16 (likewise -(128 + z) 2^e for the zero-point term).  The
+// accumulators hold u = y / c with c the m of the column's last group: before
+// group g they are multiplied by c / m[g, n] (one fp32 multiply per element;
+// the ratio lies in (1/2, 2), so u never leaves the range of y), then every
+// MFMA of group g accumulates straight into them, and y = u * c at the end.  A
+// zero scale turns the column's operands to zero (mask and magic 0) and leaves
+// c as it was.
+//
+// What bounds it.  The matrix cores with 128-row tiles (64% busy at 8192 rows:
+// 72 MFMAs a wave and group beside 340 vector instructions, 44 LDS reads);
+// vector issue with the low tiles, where a converted code word serves fewer row
+// blocks; round trips (first loads, split merge) on small grids.  So each k-step
+// issues one MFMA, then a share of the next step's conversions, LDS reads,
+// copies and sums, and the rescale of a block runs under the first two k-steps
+// of the block before it: left to the compiler, 180 vector instructions in a
+// row kept the matrix cores idle each group (gate_up, 320 rows, 160-row tile:
+// 98 us against 87 now; 8192 rows, 128 x 256: 1804 against 1684).
+// Tiles.  Four waves, two workgroups a CU, whose barriers then do not stall
+// both; eight waves where 128 x 512 tiles fill the chip (half the X copies:
+// 8192 rows 353 / 233 / 1632 / 809 us for qkv / o / gate_up / down against 366 /
+// 246 / 1697 / 850 with four).  The kernels replaced (group-sum pass, 128 x 512
+// tiles split 3 to 19 ways with a reduce pass on small grids): 372 / 252 / 1654
+// / 853 us at 8192 rows, 60 / 53 / 135 / 84 at 320 rows against 29 / 23 / 87 / 53.
+// ---------------------------------------------------------------------------
+namespace awq_md {
+constexpr int kGroupM = 8;                       // M tiles per raster group
+constexpr int kOutStride = 144;                  // bytes per row of the output transpose
+constexpr size_t kMinCounters = 1280;            // counter bytes at a workspace's start
+constexpr int kMaxSplitTiles = (int)(kMinCounters / sizeof(int));
+template <int MB, int NW>
+struct Shape {
+  static constexpr int kBM = 32 * MB;
+  static constexpr int kBN = 64 * NW;
+  static constexpr int kX = kBM * kAwqGroup * 2;           // one stage
+  static constexpr int kSP = kBM * 32;                     // pieces: [row][half][2 parts x 4]
+  static constexpr int kLds = 2 * kX + 2 * kSP;
+  // Group sums are formed in 2 MB units of (32 rows, 4 of the 8 k-steps), unit
+  // w + NW i by wave w.
+  static constexpr int kUnits = 2 * MB;
+  static constexpr int kPer = (kUnits + NW - 1) / NW;
+  static constexpr int kCopies = 8 * MB / NW;              // X copy instructions per wave
+  static_assert(NW * 32 * kOutStride <= kLds, "output transpose fits");
+};
+}  // namespace awq_md
+
+__device__ __forceinline__ float dot2_ones(uint32_t pair, float acc) {
+  const uint32_t one = 0x3F803F80u;
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair),
+                                         __builtin_bit_cast(bf16x2, one), acc, false);
+}
+
+template <int MB, int NW, bool kSplit>
+__global__ __launch_bounds__(64 * NW, MB == 1 ? 3 : MB > 4 ? 1 : 2) void
+awq_gemm_md_kernel(const bf16_t* __restrict__ x, const uint32_t* __restrict__ qw,
+                   const bf16_t* __restrict__ scales, const uint8_t* __restrict__ zeros,
+                   bf16_t* __restrict__ y, float* __restrict__ part, int* __restrict__ arrivals,
+                   int M, int N, int K, int groups_per_split, int splits, int tiles_m,
+                   int tiles_n, int tiles_per_xcd) {
+  using namespace awq_md;
+  using Sh = Shape<MB, NW>;
+  __shared__ __attribute__((aligned(16))) char lds[Sh::kLds];
   const int lane = threadIdx.x & 63, w = wave_id();
-  // tile: XCD-contiguous ranges of a grouped raster order (kGroupM M-tiles
-  // per group, N fastest within it), so the workgroups resident on one XCD
-  // share X rows and code columns in its L2
+  const int r = lane & 31, h = lane >> 5;
+  // tile: XCD-contiguous ranges of a grouped raster order (kGroupM M-tiles per
+  // group, M fastest within it), so the workgroups resident on one XCD share X
+  // rows and code columns in its L2
   int xcd, local;
   xcd_slot(blockIdx.x, xcd, local);
   const int pid = xcd * tiles_per_xcd + local;
@@ -198,225 +208,338 @@ __global__ __launch_bounds__(awq_lg::kThreads) void awq_gemm_lg_kernel(
   const int gm = min(tiles_m - first_m, kGroupM);
   const int mt = first_m + (pid % per_group) % gm;
   const int nt = (pid % per_group) / gm;
-  const int m0 = mt * kBM, n0 = nt * kBN;
+  // the last row tile ends at row M - 1 (the host picks 32 MB <= M, or MB = 1):
+  // the rows it shares with the tile before are computed twice, to the same bits
+  const int m0 = max(0, min(mt * Sh::kBM, M - Sh::kBM)), n0 = nt * Sh::kBN + 64 * w;
   const int groups = K / kAwqGroup;
   const int g_begin = blockIdx.y * groups_per_split;
   const int n_groups = min(groups, g_begin + groups_per_split) - g_begin;
+  const bool cols_in = n0 < N;                   // N is a multiple of 128: whole waves
 
-  // ---- copies of one group into one stage (each wave its share) ----
-  // Per-lane byte offsets do not depend on the group: computed once.
-  uint32_t xoff[4], woff[4];
+  // ---- per-lane byte offsets, the same for every group: copy j moves rows
+  // 4 (kCopies w + j) + lane / 16, so copies four apart differ by 16 rows ----
+  constexpr int kOffs = Sh::kCopies < 4 ? Sh::kCopies : 4;
+  uint32_t xoff[kOffs];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = 4 * (4 * w + j) + (lane >> 4);
+  for (int j = 0; j < kOffs; ++j) {
+    const int row = 4 * (Sh::kCopies * w + j) + (lane >> 4);
     const int c = (lane & 15) ^ (row & 15);
-    const int rr = min(m0 + row, M - 1) - m0;
-    xoff[j] = (uint32_t)(rr * K * 2 + c * 16);
+    // (only a batch below 32 rows has rows past M: its last row again)
+    xoff[j] = (uint32_t)((MB == 1 ? min(row, M - 1) : row) * K * 2 + c * 16);
   }
+  const int col = cols_in ? n0 + r : r;          // (columns past N compute, and store nothing)
+  const uint32_t woff = (uint32_t)(col * 64 + h * 32);
+  auto issue_x = [&](int g, int st, int j) {
+    dma16_s(x + (size_t)(m0 + 16 * (j / 4)) * K + (size_t)g * kAwqGroup, xoff[j % 4],
+            (bf16_t*)(lds + st * Sh::kX + (Sh::kCopies * w + j) * 1024));
+  };
+  struct Codes {
+    u32x4 wd[2][2];
+    uint32_t sc[2], z[2];
+  };
+  auto fetch = [&](int g, Codes& cd) {
+    const char* qb = (const char*)(qw + (size_t)g * N * 16);
+    const bf16_t* sb = scales + (size_t)g * N;
+    const uint8_t* zb = zeros + (size_t)g * N;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int cl = lane >> 2;
-    const int ch = (lane & 3) ^ ((cl >> 2) & 3);
-    const int col = min(16 * (4 * w + j) + cl, N - 1 - n0);
-    woff[j] = (uint32_t)((col * 16 + ch * 4) * 4);
-  }
-  const uint32_t spoff = (uint32_t)(min(m0 + 64 * (w & 1) + lane, M - 1) * 16);
-  const uint32_t szoff = w == 2 ? (uint32_t)(2 * min(n0 + 8 * lane, N - 8))
-                                : (uint32_t)min(n0 + 16 * lane, N - 16);
-  auto issue = [&](int g, int st) {
-    char* S = lds + st * kStage;
-    const bf16_t* xb = x + (size_t)m0 * K + (size_t)g * kAwqGroup;
+    for (int nb = 0; nb < 2; ++nb) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) dma16_s(xb, xoff[j], (bf16_t*)(S + (4 * w + j) * 1024));
-    const uint32_t* wb = qw + ((size_t)g * N + n0) * 16;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dma16_s(wb, woff[j], (bf16_t*)(S + kX + (4 * w + j) * 1024));
-    if (w < 2) {
-      dma16_s(sp + (size_t)g * M * 8, spoff, (bf16_t*)(S + kX + kW + w * 1024));
-    } else if (w == 2) {
-      dma16((const char*)(scales + (size_t)g * N) + szoff, (bf16_t*)(S + kX + kW + kSP));
-    } else if (w == 3) {
-      if (lane < 32) dma16(zeros + (size_t)g * N + szoff, (bf16_t*)(S + kX + kW + kSP + 1024));
+      for (int q = 0; q < 2; ++q)
+        cd.wd[nb][q] = *reinterpret_cast<const u32x4*>(qb + woff + nb * 2048 + q * 16);
+      cd.sc[nb] = sb[col + 32 * nb];
+      cd.z[nb] = zb[col + 32 * nb];
     }
   };
-  // The same copies one part at a time (parts 0-1: X rows, group sums, scales
-  // and zero points; parts 2-3: code words), issued at k-steps 0-3 of the
-  // previous group rather than all at once after its barrier, so that their
-  // LDS writes interleave with that group's operand reads.
-  auto issue_part = [&](int g, int st, int part) {
-    char* S = lds + st * kStage;
-    if (part < 2) {
-      const bf16_t* xb = x + (size_t)m0 * K + (size_t)g * kAwqGroup;
+
+  f32x16 u[MB][2];
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = 2 * part + jj;
-        dma16_s(xb, xoff[j], (bf16_t*)(S + (4 * w + j) * 1024));
-      }
-      if (part == 0) {
-        if (w < 2) {
-          dma16_s(sp + (size_t)g * M * 8, spoff, (bf16_t*)(S + kX + kW + w * 1024));
-        } else if (w == 2) {
-          dma16((const char*)(scales + (size_t)g * N) + szoff, (bf16_t*)(S + kX + kW + kSP));
-        } else if (w == 3) {
-          if (lane < 32) dma16(zeros + (size_t)g * N + szoff, (bf16_t*)(S + kX + kW + kSP + 1024));
-        }
-      }
-    } else {
-      const uint32_t* wb = qw + ((size_t)g * N + n0) * 16;
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = 2 * (part - 2) + jj;
-        dma16_s(wb, woff[j], (bf16_t*)(S + kX + (4 * w + j) * 1024));
-      }
-    }
-  };
-  const int r = lane & 31, h = lane >> 5;
-  f32x16 u[4][2];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < MB; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int j = 0; j < 16; ++j) u[a][b][j] = 0.f;
   float cref[2] = {1.f, 1.f};
+  uint32_t nz[2] = {0, 0};                       // zero-point operands of the previous group
 
-  if (n_groups > 0) issue(g_begin, 0);
-  for (int it = 0; it < n_groups; ++it) {
-    // this group's copies have landed (the only ones in flight) and every
-    // wave is done with the stage the next group's copies overwrite
-    wait_vm<0>();
-    __syncthreads();
-    const bool more = it + 1 < n_groups;
-    const int g_next = g_begin + it + 1, st_next = (it + 1) % kStages;
-    const char* S = lds + (it % kStages) * kStage;
-    const char* SX = S;
-    const char* SW = S + kX;
-    const char* SPc = S + kX + kW;
-    const char* SZ = S + kX + kW + kSP;
+  char* const SP = lds + 2 * Sh::kX;
 
-    float rho[2];
-    uint32_t mask[2], magic[2];
-    bf16x8 bz[2];
-    u32x4 words[2][2];
+  Codes next;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const int cl = 64 * w + 32 * nb + r;
-      const ColScale cs = col_scale(*reinterpret_cast<const uint16_t*>(SZ + 2 * cl),
-                                    (uint8_t)SZ[1024 + cl]);
-      const bool zero = cs.mask == 0u;
-      rho[nb] = zero ? 1.f : cref[nb] * __builtin_amdgcn_rcpf(cs.c);
-      cref[nb] = zero ? cref[nb] : cs.c;
-      mask[nb] = in_vgpr(cs.mask);
-      magic[nb] = in_vgpr(cs.magic);
-      u32x4 b;
-      b[0] = cs.nz | (cs.nz << 16);
-      b[1] = cs.nz;
-      b[2] = 0;
-      b[3] = 0;
-      bz[nb] = as_bf16x8(b);
-      const int blk = cl >> 4, ci = cl & 15;
+  for (int j = 0; j < Sh::kCopies; ++j) issue_x(g_begin, 0, j);
+  fetch(g_begin, next);
+  for (int i = threadIdx.x; i < 2 * Sh::kSP / 16; i += (64 * NW))
+    *reinterpret_cast<u32x4*>(SP + i * 16) = u32x4{0, 0, 0, 0};
+
+  // u += (previous group's sums) (its -(128 + z) 2^e); pieces of slot `slot`
+  auto zero_term = [&](int slot) {
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int ch = (2 * h + q) ^ ((ci >> 2) & 3);
-        words[nb][q] = *reinterpret_cast<const u32x4*>(SW + blk * 1024 + ci * 64 + ch * 16);
-      }
-    }
-    auto a_op = [&](int mb, int t) {
-      return as_bf16x8(*reinterpret_cast<const u32x4*>(
-          SX + (32 * mb + r) * 256 + (((2 * t + h) ^ (r & 15)) * 16)));
-    };
-    bf16x8 acur[4];
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) acur[mb] = a_op(mb, 0);
-    // u <- u * c / m, then the group's MFMAs accumulate into u
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      u32x4 v = *reinterpret_cast<const u32x4*>(SPc + (32 * mb + r) * 16);
-      if (h) v = u32x4{0, 0, 0, 0};
+    for (int mb = 0; mb < MB; ++mb) {
+      const bf16x8 v = as_bf16x8(*reinterpret_cast<const u32x4*>(
+          SP + slot * Sh::kSP + (32 * mb + r) * 32 + h * 16));
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) u[mb][nb][j] *= rho[nb];
-        u[mb][nb] = mfma32(as_bf16x8(v), bz[nb], u[mb][nb]);
+        const u32x4 b = {nz[nb], nz[nb], nz[nb], nz[nb]};
+        u[mb][nb] = mfma32(v, as_bf16x8(b), u[mb][nb]);
       }
     }
+  };
+
+  for (int it = 0; it < n_groups; ++it) {
+    // this group's copies have landed and every wave is done with the stage
+    // that the next group's copies overwrite
+    wait_vm<0>();
+    __syncthreads();
+    const Codes cd = next;
+    const int g_next = g_begin + min(it + 1, n_groups - 1);   // (the last group again: unused)
+    const char* SX = lds + (it & 1) * Sh::kX;
+    auto a_op = [&](int row, int t) {
+      return as_bf16x8(*reinterpret_cast<const u32x4*>(
+          SX + row * 256 + (((2 * t + h) ^ (row & 15)) * 16)));
+    };
+    bf16x8 zp[MB], acur[MB], anxt[MB];
+    const char* spr = SP + ((it + 1) & 1) * Sh::kSP + r * 32 + h * 16;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      // one k-step at a time (the A operands of step t + 1 are loaded during
-      // step t, no earlier: the accumulators need the registers)
+    for (int mb = 0; mb < MB; ++mb)
+      zp[mb] = as_bf16x8(*reinterpret_cast<const u32x4*>(spr + mb * 1024));
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acur[mb] = a_op(32 * mb + r, 0);
+    // ---- the previous group's zero-point term (zero pieces before the first
+    // group), beside the columns' constants and the first code operands ----
+    float rho[2];
+    uint32_t mask[2], magic[2];
+    u32x4 bcur[2], bnxt[2];
+    const u32x4 bz[2] = {{nz[0], nz[0], nz[0], nz[0]}, {nz[1], nz[1], nz[1], nz[1]}};
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      ColScale cs = col_scale_plain(cd.sc[nb], cd.z[nb]);
+      rho[nb] = cref[nb] * __builtin_amdgcn_rcpf(cs.c);
+      if (__builtin_expect(wave_any(!plain_scale(cd.sc[nb])), 0)) {
+        asm volatile("");                        // (not executed and selected)
+        cs = col_scale(cd.sc[nb], cd.z[nb]);
+        rho[nb] = cs.mask == 0u ? 1.f : cref[nb] * __builtin_amdgcn_rcpf(cs.c);
+        if (cs.mask == 0u) cs.c = cref[nb];
+      }
+      cref[nb] = cs.c;
+      mask[nb] = in_vgpr(cs.mask);
+      magic[nb] = in_vgpr(cs.magic);
+      nz[nb] = cs.nz | (cs.nz << 16);
+    }
+    // pair p of the code operand of k-step t
+    auto code_pair = [&](int nb, int t, int p) {
+      return ((cd.wd[nb][t & 1][t >> 1] >> (4 * p)) & mask[nb]) | magic[nb];
+    };
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 2 * MB; ++i) {
+      const int mb = i >> 1, nb = i & 1;
+      u[mb][nb] = mfma32(zp[mb], as_bf16x8(bz[nb]), u[mb][nb]);
+#pragma unroll
+      for (int e = i * 16 / (2 * MB); e < (i + 1) * 16 / (2 * MB); ++e) {
+        if (e < 8) bcur[e >> 2][e & 3] = code_pair(e >> 2, 0, e & 3);
+        else bnxt[(e >> 2) & 1][e & 3] = code_pair((e >> 2) & 1, 1, e & 3);
+      }
+      if (nb == 1) anxt[mb] = a_op(32 * mb + r, 1);
       __builtin_amdgcn_sched_barrier(0);
-      if (t < 4 && more) issue_part(g_next, st_next, t);
-      bf16x8 anxt[4];
-      if (t < 7) {
+    }
+    // ---- u <- u c / m, block by block under the MFMAs of k-steps 0 and 1 of
+    // the block before ----
+    auto rescale = [&](int i, int part) {
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) anxt[mb] = a_op(mb, t + 1);
-      }
-      bf16x8 b[2];
+      for (int j = 8 * part; j < 8 * part + 8; ++j) u[i >> 1][i & 1][j] *= rho[i & 1];
+    };
+    float sums[Sh::kPer][2];
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-        b[nb] = codes_to_bf16(words[nb][t & 1][t >> 1], mask[nb], magic[nb]);
+    for (int i = 0; i < Sh::kPer; ++i) sums[i][0] = sums[i][1] = 0.f;
+    // sum unit i (even ones in steps 0-3, odd ones in 4-7): rows 32 (id / 2),
+    // k-steps 4 (id % 2) + t % 4
+    u32x4 sf[Sh::kPer];
+    auto sum_read = [&](int t) {
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+      for (int i = 0; i < Sh::kPer; ++i)
+        if ((i & 1) == (t >> 2)) {
+          const int id = (w + NW * i) % Sh::kUnits;
+          sf[i] = as_u32x4(a_op(32 * (id >> 1) + r, 4 * (id & 1) + (t & 3)));
+        }
+    };
+    auto sum_add = [&](int t) {
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) u[mb][nb] = mfma32(acur[mb], b[nb], u[mb][nb]);
-      if (t < 7) {
+      for (int i = 0; i < Sh::kPer; ++i)
+        if ((i & 1) == (t >> 2)) {
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) acur[mb] = anxt[mb];
+          for (int e = 0; e < 4; ++e) sums[i][e & 1] = dot2_ones(sf[i][e], sums[i][e & 1]);
+        }
+    };
+    auto pieces = [&](int i) {
+      const int id = w + NW * i;
+      const float s = sums[i][0] + sums[i][1];
+      const __bf16 p1 = (__bf16)s;
+      const float d1 = s - (float)p1;
+      const __bf16 p2 = (__bf16)d1;
+      const __bf16 p3 = (__bf16)(d1 - (float)p2);
+      const u32x2 pc = {(uint32_t)__builtin_bit_cast(uint16_t, p1) |
+                            ((uint32_t)__builtin_bit_cast(uint16_t, p2) << 16),
+                        (uint32_t)__builtin_bit_cast(uint16_t, p3)};
+      // (an opaque lane: the address is formed here, not kept over the loop)
+      const int ln = (int)in_vgpr(threadIdx.x) & 63;
+      if (id < Sh::kUnits)
+        *reinterpret_cast<u32x2*>(SP + (it & 1) * Sh::kSP + 1024 * (id >> 1) + 8 * (id & 1) +
+                                  (ln & 31) * 32 + (ln >> 5) * 16) = pc;
+    };
+    rescale(0, 0);
+    rescale(0, 1);
+    bf16x8 a2[MB];
+#pragma unroll
+    for (int i = 0; i < 2 * MB; ++i) {
+      const int mb = i >> 1, nb = i & 1;
+      __builtin_amdgcn_sched_barrier(0);
+      u[mb][nb] = mfma32(acur[mb], as_bf16x8(bcur[nb]), u[mb][nb]);
+      if (i + 1 < 2 * MB) rescale(i + 1, 0);
+      if (i == 0) sum_read(0);
+      __builtin_amdgcn_sched_barrier(0);
+      u[mb][nb] = mfma32(anxt[mb], as_bf16x8(bnxt[nb]), u[mb][nb]);
+      if (i + 1 < 2 * MB) rescale(i + 1, 1);
+      if (nb == 1) a2[mb] = a_op(32 * mb + r, 2);
+      if (i == 2 * MB - 1) {
+        sum_add(0);
+        sum_read(1);
       }
     }
-  }
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(g_next, next);                         // (no earlier: registers)
+    sum_add(1);
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+    for (int e = 0; e < 8; ++e) bcur[e >> 2][e & 3] = code_pair(e >> 2, 2, e & 3);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acur[mb] = a2[mb];
+    // ---- k-steps 2 to 7: one MFMA, then a share of the next step's operands,
+    // the sums and the next group's copies ----
+#pragma unroll
+    for (int t = 2; t < 8; ++t) {
+      sum_read(t);
+#pragma unroll
+      for (int i = 0; i < 2 * MB; ++i) {
+        const int mb = i >> 1, nb = i & 1;
+        __builtin_amdgcn_sched_barrier(0);
+        u[mb][nb] = mfma32(acur[mb], as_bf16x8(bcur[nb]), u[mb][nb]);
+        if (t < 7) {
+#pragma unroll
+          for (int e = i * 8 / (2 * MB); e < (i + 1) * 8 / (2 * MB); ++e)
+            bnxt[e >> 2][e & 3] = code_pair(e >> 2, t + 1, e & 3);
+          if (nb == 1) anxt[mb] = a_op(32 * mb + r, t + 1);
+        }
+        if (i == 2 * MB - 1) sum_add(t);
+        if (i < Sh::kCopies && t >= 2 && t < 6 && i * 4 / Sh::kCopies == t - 2)
+          issue_x(g_next, (it + 1) & 1, i);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (Sh::kPer > 1 && t == 4) pieces(0);
+      if (t < 7) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acur[mb] = anxt[mb];
+        bcur[0] = bnxt[0];
+        bcur[1] = bnxt[1];
+      }
+    }
+#pragma unroll
+    for (int i = 1; i < Sh::kPer; ++i) pieces(i);
+    if constexpr (Sh::kPer == 1) pieces(0);
+  }
+  wait_vm<0>();                                  // (the last, unused copies)
+  __syncthreads();
+  zero_term((n_groups + 1) & 1);
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int j = 0; j < 16; ++j) u[mb][nb][j] *= cref[nb];
 
-  // ---- output ----
-  const bool cols_in = n0 + 64 * w < N;
+  // ---- groups split over workgroups: fp32 partials (device-coherent stores,
+  // another XCD may add them), then the last workgroup of the tile to arrive
+  // adds them in split order, its own from registers, and leaves the tile's
+  // counter at zero ----
   if constexpr (kSplit) {
-    if (!cols_in) return;
+    constexpr int kVals = MB * 32;               // values per lane
+    const size_t per_split = (size_t)NW * 64 * kVals;
+    float* mine = part + ((size_t)pid * splits + blockIdx.y) * per_split +
+                  (size_t)w * 64 * kVals + 2 * lane;
+    if (cols_in) {
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int row = m0 + 32 * mb + 8 * (j >> 2) + 4 * h + (j & 3);
-          if (row < M)
-            part[((size_t)blockIdx.y * M + row) * N + n0 + 64 * w + 32 * nb + r] = u[mb][nb][j];
-        }
-  } else {
-    // transpose through LDS so that each lane stores 16 contiguous bytes,
-    // 64 rows at a time
-    __syncthreads();
-    char* T = lds + w * 64 * kOutStride;
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-#pragma unroll
-      for (int mh = 0; mh < 2; ++mh)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            const int row = 32 * mh + 8 * (j >> 2) + 4 * h + (j & 3);
-            const __bf16 v = (__bf16)u[2 * half + mh][nb][j];
-            *reinterpret_cast<__bf16*>(T + row * kOutStride + 2 * (32 * nb + r)) = v;
-          }
-      wave_lds_sync();
-      if (cols_in) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int idx = 64 * i + lane;
-          const int row = idx >> 3, ch = idx & 7;
-          const int grow = m0 + 64 * half + row;
-          const u32x4 v = *reinterpret_cast<const u32x4*>(T + row * kOutStride + ch * 16);
-          if (grow < M)
-            *reinterpret_cast<u32x4*>(y + (size_t)grow * N + n0 + 64 * w + 8 * ch) = v;
-        }
-      }
-      wave_lds_sync();
+          for (int j = 0; j < 16; j += 2)
+            store_coherent2(mine + ((mb * 2 + nb) * 16 + j) * 64, u[mb][nb][j], u[mb][nb][j + 1]);
     }
+    wait_all_memory();
+    __syncthreads();
+    int* flag = reinterpret_cast<int*>(lds);
+    if (threadIdx.x == 0)
+      *flag = __hip_atomic_fetch_add(arrivals + pid, 1, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int arrived = *flag;
+    __syncthreads();                             // flag read: the LDS is free again
+    if (arrived != splits - 1) return;
+    if (threadIdx.x == 0)
+      __hip_atomic_store(arrivals + pid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // (the partials of four splits and one row block in flight at a time: a
+    // load takes a round trip to the coherence point)
+    const float* tile = part + (size_t)pid * splits * per_split + (size_t)w * 64 * kVals + 2 * lane;
+    constexpr int kBatch = 4;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      float acc[32];
+#pragma unroll
+      for (int j = 0; j < 32; ++j) acc[j] = 0.f;
+      for (int s0 = 0; s0 < splits; s0 += kBatch) {
+        float v[kBatch][32];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+          for (int j = 0; j < 32; j += 2) {
+            float p[2];
+            load_coherent_vec<2>(tile + (size_t)min(s0 + b, splits - 1) * per_split +
+                                     (mb * 32 + j) * 64, p);
+            v[b][j] = p[0];
+            v[b][j + 1] = p[1];
+          }
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+          for (int j = 0; j < 32; ++j) acc[j] += s0 + b < splits ? v[b][j] : 0.f;
+      }
+#pragma unroll
+      for (int j = 0; j < 32; ++j) u[mb][j >> 4][j & 15] = acc[j];
+    }
+  }
+
+  // ---- output: transposed through LDS so that each lane stores 16 contiguous
+  // bytes, 32 rows at a time ----
+  if constexpr (!kSplit) __syncthreads();
+  char* T = lds + w * 32 * kOutStride;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int row = 8 * (j >> 2) + 4 * h + (j & 3);
+        *reinterpret_cast<__bf16*>(T + row * kOutStride + 2 * (32 * nb + r)) = (__bf16)u[mb][nb][j];
+      }
+    wave_lds_sync();
+    if (cols_in) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int idx = 64 * i + lane;
+        const int row = idx >> 3, ch = idx & 7;
+        const int grow = m0 + 32 * mb + row;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(T + row * kOutStride + ch * 16);
+        if (MB > 1 || grow < M) *reinterpret_cast<u32x4*>(y + (size_t)grow * N + n0 + 8 * ch) = v;
+      }
+    }
+    wave_lds_sync();
   }
 }
 
@@ -698,18 +821,6 @@ __global__ __launch_bounds__(kWaves * 64) void awq_gemm_sm_kernel(
   }
 }
 
-// Y = sum of the split partials in split order, rounded to bf16.
-__global__ __launch_bounds__(256) void awq_reduce_kernel(const float* __restrict__ part,
-                                                         bf16_t* __restrict__ y, int64_t MN,
-                                                         int splits) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= MN) return;
-  float acc = 0.f;
-  for (int s = 0; s < splits; ++s) acc += part[(size_t)s * MN + i];
-  const __bf16 v = (__bf16)acc;
-  y[i] = __builtin_bit_cast(bf16_t, v);
-}
-
 // RAG_AWQ_SM_NB / RAG_AWQ_SM_SPLITS (read at each call) fix the small-batch
 // column blocks per workgroup (2, 4 or 8, at most 8 / row blocks) and the split of the groups: a
 // testing and tuning knob (any choice computes the same sums; only split
@@ -719,26 +830,84 @@ static int env_int(const char* name) {
   return (e != nullptr && e[0] != 0) ? std::atoi(e) : 0;
 }
 
+// The tiles of awq_gemm_md_kernel and what they cost: kRes workgroups fit a CU
+// (registers); one group step takes kStep us with one of them resident and
+// kStep + (n - 1) kMore with n.
+struct MdTile {
+  int mb, nw, res;
+  double step, more;
+};
+static constexpr MdTile kMdTiles[] = {{1, 4, 3, 0.84, 0.47}, {2, 4, 2, 1.13, 0.78},
+                                      {3, 4, 2, 1.57, 1.15}, {4, 4, 2, 1.91, 1.56},
+                                      {5, 4, 1, 2.66, 0},    {4, 8, 1, 3.35, 0}};
+
+// Estimated time (us) of a launch: the busiest CU's n workgroups run in batches
+// of kRes.  A split adds the partials' trip (written once, read once by the
+// merging workgroups) and the merge's round trips.  Constants fitted to 1,900
+// timings (M 33-4096, the 7B layers and generic shapes): 8% rms off, and the
+// choice is on average 2% slower than the best of all (tile, split) pairs.
+static double awq_md_cost(const MdTile& c, int64_t tiles, int splits, int groups_per_split,
+                          int64_t mn) {
+  const int64_t n = (tiles * splits + kAwqCus - 1) / kAwqCus;      // on the busiest CU
+  const int64_t full = n / c.res, rest = n % c.res;
+  const double step = full * (c.step + c.more * (c.res - 1)) +
+                      (rest ? c.step + c.more * (rest - 1) : 0);
+  double t = step * groups_per_split;
+  if (splits > 1) t += 2.7 + 0.78e-6 * splits * mn + 0.52 * (splits - 1) * c.mb;
+  return t;
+}
+
 AwqPlan awq_plan(int M, int N, int K) {
   AwqPlan p{};
   p.groups = K / kAwqGroup;
-  p.large = M > 64;
   const size_t up = 255;
   p.splits = 1;
   p.groups_per_split = p.groups;
-  if (p.large) {
-    p.sp_bytes = ((size_t)p.groups * M * 16 + up) & ~up;
-    p.tiles_m = (M + awq_lg::kBM - 1) / awq_lg::kBM;
-    p.tiles_n = (N + awq_lg::kBN - 1) / awq_lg::kBN;
-    p.tiles = (int64_t)p.tiles_m * p.tiles_n;
-    p.tiles_per_xcd = (int)((p.tiles + kNumXcd - 1) / kNumXcd);
-    // fewer tiles than CUs: split the groups (partials + a reduce pass)
-    if (p.tiles < kAwqCus) {
-      const int splits = (int)std::min<int64_t>(p.groups, (2 * kAwqCus) / p.tiles);
-      p.groups_per_split = (p.groups + splits - 1) / splits;
-      p.splits = (p.groups + p.groups_per_split - 1) / p.groups_per_split;
+  // awq_gemm_sm_kernel for up to 64 rows except where its tiles are the slower
+  // ones: 33-64 rows of a layer above the 7B o_proj's size (7B gate_up at 64
+  // rows 49 us against 29, o_proj 14.0 against 15.1), 17-32 rows of a wide one
+  // (gate_up at 32 rows 27 against 20, N = 12288 15.7 either way).
+  const bool knobs = env_int("RAG_AWQ_SM_NB") > 0 || env_int("RAG_AWQ_SM_SPLITS") > 0;
+  const bool wide = (M > 32 && (int64_t)N * K >= (int64_t)4608 * 4096) || (M > 16 && N > 16384);
+  if (M > 64 || (wide && !knobs)) {
+    double best = 0;
+    for (const MdTile& c : kMdTiles) {
+      if (c.mb > 1 && 32 * c.mb > M) continue;
+      const int tiles_m = (M + 32 * c.mb - 1) / (32 * c.mb);
+      const int tiles_n = (N + 64 * c.nw - 1) / (64 * c.nw);
+      const int64_t tiles = (int64_t)tiles_m * tiles_n;
+      for (int want = 1; want <= 16 && want <= p.groups; ++want) {
+        if (want > 1 && (tiles > awq_md::kMaxSplitTiles || c.nw != 4)) break;
+        const int gps = (p.groups + want - 1) / want;
+        const int splits = (p.groups + gps - 1) / gps;
+        if (splits != want) continue;
+        const double t = awq_md_cost(c, tiles, splits, gps, (int64_t)M * N);
+        if (p.md_mb == 0 || t < best) {
+          best = t;
+          p.md_mb = c.mb;
+          p.md_nw = c.nw;
+          p.tiles_m = tiles_m;
+          p.tiles_n = tiles_n;
+          p.tiles = tiles;
+          p.splits = splits;
+          p.groups_per_split = gps;
+        }
+      }
     }
-    p.part_bytes = p.splits > 1 ? (((size_t)p.splits * M * N * sizeof(float) + up) & ~up) : 0;
+    p.tiles_per_xcd = (int)((p.tiles + kNumXcd - 1) / kNumXcd);
+    // Counters, then the partials.  Every shape keeps its counters in the
+    // workspace's first kMinCounters bytes and its partials behind them, so
+    // that calls of different shapes can follow each other in one workspace.
+    // (More than 64 rows: sized as group sums of x and whole [M, N] planes.)
+    p.counter_bytes = M > 64 ? ((size_t)p.groups * M * 16 + up) & ~up : awq_md::kMinCounters;
+    if (p.splits > 1) {
+      const size_t part = (size_t)p.splits * p.tiles * (32 * p.md_mb) * (64 * p.md_nw) *
+                          sizeof(float);
+      const size_t plane = (size_t)M * N * sizeof(float);
+      p.part_bytes = (part + plane - 1) / plane * plane;
+    } else if (M <= 64) {
+      p.counter_bytes = 0;
+    }
     return p;
   }
   // Small batches: a workgroup stages X of at most kXCap 16-row blocks, so
@@ -780,43 +949,41 @@ AwqPlan awq_plan(int M, int N, int K) {
   if (p.splits > 1) {
     // arrival counters first: zero-filled once by the caller, left zero by
     // every call
-    p.counter_bytes = ((size_t)p.tiles_n * sizeof(int) + up) & ~up;
+    p.counter_bytes = std::max<size_t>(awq_md::kMinCounters,
+                                       ((size_t)p.tiles_n * sizeof(int) + up) & ~up);
     p.part_bytes = ((size_t)p.splits * M * N * sizeof(float) + up) & ~up;
   }
   return p;
 }
 
-hipError_t launch_awq_gemm(const AwqArgs& a, hipStream_t stream) {
-  const AwqPlan p = awq_plan(a.M, a.N, a.K);
+hipError_t launch_awq_gemm(const AwqArgs& a, const AwqPlan& p, hipStream_t stream) {
   char* ws = static_cast<char*>(a.workspace);
   const bf16_t* x = (const bf16_t*)a.x;
   const uint32_t* qw = (const uint32_t*)a.qweight;
   const bf16_t* sc = (const bf16_t*)a.scales;
   bf16_t* y = (bf16_t*)a.y;
-  if (p.large) {
-    bf16_t* sp = reinterpret_cast<bf16_t*>(ws);
-    float* part = reinterpret_cast<float*>(ws + p.sp_bytes);
-    const int64_t nsum = (int64_t)p.groups * a.M * 16;   // 16 lanes per row
-    hipLaunchKernelGGL(awq_group_sums_kernel, dim3((unsigned)((nsum + 255) / 256)), dim3(256), 0,
-                       stream, x, sp, a.M, a.K);
+  int* counters = reinterpret_cast<int*>(ws);
+  float* part = reinterpret_cast<float*>(ws + p.counter_bytes);
+  if (p.md_mb > 0) {
     const dim3 grid((unsigned)(p.tiles_per_xcd * kNumXcd), (unsigned)p.splits);
-    if (p.splits > 1) {
-      hipLaunchKernelGGL(awq_gemm_lg_kernel<true>, grid, dim3(awq_lg::kThreads), 0, stream, x, qw,
-                         sc, a.zeros, sp, y, part, a.M, a.N, a.K, p.groups_per_split, p.tiles_m,
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(p.md_nw * 64), 0, stream, x, qw, sc, a.zeros, y,
+                         part, counters, a.M, a.N, a.K, p.groups_per_split, p.splits, p.tiles_m,
                          p.tiles_n, p.tiles_per_xcd);
-      const int64_t mn = (int64_t)a.M * a.N;
-      hipLaunchKernelGGL(awq_reduce_kernel, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0,
-                         stream, part, y, mn, p.splits);
-    } else {
-      hipLaunchKernelGGL(awq_gemm_lg_kernel<false>, grid, dim3(awq_lg::kThreads), 0, stream, x,
-                         qw, sc, a.zeros, sp, y, part, a.M, a.N, a.K, p.groups_per_split,
-                         p.tiles_m, p.tiles_n, p.tiles_per_xcd);
+    };
+    const bool split = p.splits > 1;
+    switch (p.md_mb * 10 + p.md_nw) {
+      case 14: split ? go(awq_gemm_md_kernel<1, 4, true>) : go(awq_gemm_md_kernel<1, 4, false>); break;
+      case 24: split ? go(awq_gemm_md_kernel<2, 4, true>) : go(awq_gemm_md_kernel<2, 4, false>); break;
+      case 34: split ? go(awq_gemm_md_kernel<3, 4, true>) : go(awq_gemm_md_kernel<3, 4, false>); break;
+      case 44: split ? go(awq_gemm_md_kernel<4, 4, true>) : go(awq_gemm_md_kernel<4, 4, false>); break;
+      case 54: split ? go(awq_gemm_md_kernel<5, 4, true>) : go(awq_gemm_md_kernel<5, 4, false>); break;
+      case 48: go(awq_gemm_md_kernel<4, 8, false>); break;
+      default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
   }
   if ((int64_t)p.groups_per_split * p.sm_mb > awq_sm::kXCap) return hipErrorInvalidValue;
-  int* counters = reinterpret_cast<int*>(ws);
-  float* part = reinterpret_cast<float*>(ws + p.counter_bytes);
   const dim3 grid((unsigned)p.tiles_n, (unsigned)p.splits), block(512);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, 0, stream, x, qw, sc, a.zeros, y, part, counters,

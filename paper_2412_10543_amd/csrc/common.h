@@ -86,6 +86,11 @@ __device__ __forceinline__ void store_coherent(float* p, float v) {
 __device__ __forceinline__ float load_coherent(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void store_coherent2(float* p, float a, float b) {
+  const f32x2 v = {a, b};
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, v),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 // N consecutive floats (N = 1 or 2, naturally aligned) in one such load.
 template <int N>
 __device__ __forceinline__ void load_coherent_vec(const float* p, float (&v)[N]) {
