@@ -487,9 +487,8 @@ size_t rag_awq_workspace_size(int32_t M, int32_t N, int32_t K,
  *   workspace  device, >= rag_awq_workspace_size(M, N, K, group_size) bytes,
  *            256-byte aligned, zero-filled once before its first use: it
  *            starts with the arrival counters of a split over the weight
- *            groups, which every call leaves at zero again.  Calls of any
- *            shapes may follow each other in one; overlapping calls must not
- *            share it.
+ *            groups, which every call leaves at zero again.  Overlapping
+ *            calls must not share it.
  * Returns RAG_OK (M == 0 is a no-op; x and y may then be NULL),
  * RAG_ERR_INVALID_ARG (null pointer, a pointer not 16-byte aligned, negative
  * M, N or K not positive), RAG_ERR_UNSUPPORTED (group_size not 128, K or N not a multiple of

@@ -895,11 +895,14 @@ AwqPlan awq_plan(int M, int N, int K) {
       }
     }
     p.tiles_per_xcd = (int)((p.tiles + kNumXcd - 1) / kNumXcd);
-    // Counters, then the partials.  Every shape keeps its counters in the
-    // workspace's first kMinCounters bytes and its partials behind them, so
-    // that calls of different shapes can follow each other in one workspace.
-    // (More than 64 rows: sized as group sums of x and whole [M, N] planes.)
-    p.counter_bytes = M > 64 ? ((size_t)p.groups * M * 16 + up) & ~up : awq_md::kMinCounters;
+    // Counters, then the partials.  The counters lie in the workspace's first
+    // kMinCounters bytes and the partials behind those and behind the counters
+    // that the small kernel may use for the same layer, so that batches of
+    // different sizes can follow each other in one workspace.  (More than 64
+    // rows: sized as group sums of x and whole [M, N] planes.)
+    p.counter_bytes = M > 64 ? ((size_t)p.groups * M * 16 + up) & ~up
+                             : std::max<size_t>(awq_md::kMinCounters,
+                                                ((size_t)N / 128 * sizeof(int) + up) & ~up);
     if (p.splits > 1) {
       const size_t part = (size_t)p.splits * p.tiles * (32 * p.md_mb) * (64 * p.md_nw) *
                           sizeof(float);
