@@ -1,5 +1,6 @@
 // gfx950 kernels of the RAG-synthesis attention path and their launchers:
-//   prefill_varlen_kernel  packed variable-length prefill (dense K/V)
+//   prefill_varlen_kernel  packed variable-length prefill (dense K/V), several
+//                          query tiles per workgroup; prefill_single_kernel: one
 //   paged_decode_kernel    decode rows against a paged KV cache (split-KV
 //                          partials are merged inside it by the last split
 //                          of each sequence to finish)
@@ -209,6 +210,51 @@ __global__ __launch_bounds__(64 * kPfWavesDense, 2) void prefill_varlen_kernel(
                                min(q0 + rows, nk));
     }
   }
+}
+
+// The same with one query tile per workgroup: no item boundaries, and the tiles
+// with the most keys are dispatched first, as nothing else evens out a launch
+// of few workgroups (one prompt of 3.1k tokens 106 us in ascending order, 88 so;
+// 4.7k 202 -> 185, 6.2k 320 -> 301; 288 tokens of 4 heads 10.8 -> 9.8).
+template <int D>
+__global__ __launch_bounds__(64 * kPfWavesDense, 2) void prefill_single_kernel(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+    const bf16_t* __restrict__ v, bf16_t* __restrict__ o, float* __restrict__ lse,
+    const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, int num_seqs,
+    int hq, int hkv, int n_qt, float scale, int causal, bf16_t* __restrict__ k_cache,
+    bf16_t* __restrict__ v_cache, const int32_t* __restrict__ slots) {
+  __shared__ __attribute__((aligned(16))) bf16_t st0[ChunkLayout<D>::kElemsTile];
+  __shared__ __attribute__((aligned(16))) bf16_t st1[ChunkLayout<D>::kElemsTile];
+  __shared__ __attribute__((aligned(16))) bf16_t st2[ChunkLayout<D>::kElemsTile];
+  __shared__ __attribute__((aligned(16))) bf16_t st3[ChunkLayout<D>::kElemsTile];
+  const int group = hq / hkv;
+  const TileCoord tc = prefill_coord(blockIdx.x, num_seqs * hkv, hkv, group, n_qt);
+  if (!tc.valid) return;
+  const int qb = cu_q[tc.seq], nq = cu_q[tc.seq + 1] - qb;
+  const int kb = cu_k[tc.seq], nk = cu_k[tc.seq + 1] - kb;
+  const int rows = pf_rows_per_tile(group, kPfWavesDense);
+  const int q0 = (n_qt - 1 - tc.j) * rows;
+  if (q0 >= nq) return;
+  const int tq = cu_q[num_seqs];
+  PfGroup g;
+  g.q = q + ((size_t)qb * hq + tc.h0) * D;
+  g.o = o + ((size_t)qb * hq + tc.h0) * D;
+  g.lse = lse ? lse + (size_t)tc.h0 * tq + qb : nullptr;
+  g.q_stride = (size_t)hq * D;
+  g.lse_stride = (size_t)tq;
+  g.hw = pf_heads_per_wg(group);
+  g.nq = nq;
+  g.nk = nk;
+  g.wg_rows = rows;
+  g.causal = causal;
+  g.scale = scale;
+  const DenseKV kv{k + ((size_t)kb * hkv + tc.kvh) * D, v + ((size_t)kb * hkv + tc.kvh) * D,
+                   (size_t)hkv * D};
+  prefill_tile_pipe<D, kPfWavesDense, DenseKV>(g, kv, q0, st0, st1, st2, st3);
+  if (slots != nullptr && tc.h0 == tc.kvh * group)
+    prefill_rows_to_cache<D>(kv.k, kv.v, kv.stride, k_cache + (size_t)tc.kvh * 16 * D,
+                             v_cache + (size_t)tc.kvh * 16 * D, (size_t)hkv * 16 * D, slots + kb,
+                             q0, min(q0 + rows, nk));
 }
 
 // ---------------------------------------------------------------------------
@@ -434,11 +480,18 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
   }
 }
 
-template <int D, bool kAppend, int kChunks>
-__global__ __launch_bounds__(kDecThreads, 2) void paged_decode_balanced_kernel(
-    PagedKernelArgs a) {
+// Up to 64 rows, and up to kBalMaxRows.
+template <int D, bool kAppend>
+__global__ __launch_bounds__(kDecThreads, 2) void paged_decode_balanced_kernel(PagedKernelArgs a) {
   __shared__ __attribute__((aligned(16))) bf16_t lds[DecLds<D>::kBytes / 2];
-  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, kChunks>(
+  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, 1>(
+      a, blockIdx.x, a.hq / a.hkv, (size_t)a.hkv * 16 * D, lds);
+}
+
+template <int D, bool kAppend>
+__global__ __launch_bounds__(kDecThreads, 2) void paged_decode_balanced_rows_kernel(PagedKernelArgs a) {
+  __shared__ __attribute__((aligned(16))) bf16_t lds[DecLds<D>::kBytes / 2];
+  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, kBalMaxChunks>(
       a, blockIdx.x, a.hq / a.hkv, (size_t)a.hkv * 16 * D, lds);
 }
 
@@ -511,11 +564,18 @@ static hipError_t launch_prefill_d(const PrefillArgs& a, hipStream_t stream) {
   const PfSplit sp = pf_split(a.num_seqs, a.hkv, group, a.max_seqlen_q, true);
   const int64_t grid = tile_grid(a.num_seqs, a.hkv, group, sp);
   if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL(prefill_varlen_kernel<D>, dim3((unsigned)grid), dim3(64 * kPfWavesDense), 0,
-                     stream,
-                     (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o,
-                     a.lse, a.cu_q, a.cu_k, a.num_seqs, a.hq, a.hkv, sp.items, sp.per, a.scale,
-                     a.causal, (bf16_t*)a.k_cache, (bf16_t*)a.v_cache, a.slots);
+  if (sp.items > 1)
+    hipLaunchKernelGGL(prefill_varlen_kernel<D>, dim3((unsigned)grid), dim3(64 * kPfWavesDense), 0,
+                       stream,
+                       (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o,
+                       a.lse, a.cu_q, a.cu_k, a.num_seqs, a.hq, a.hkv, sp.items, sp.per, a.scale,
+                       a.causal, (bf16_t*)a.k_cache, (bf16_t*)a.v_cache, a.slots);
+  else
+    hipLaunchKernelGGL(prefill_single_kernel<D>, dim3((unsigned)grid), dim3(64 * kPfWavesDense), 0,
+                       stream,
+                       (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, (bf16_t*)a.o,
+                       a.lse, a.cu_q, a.cu_k, a.num_seqs, a.hq, a.hkv, sp.n_qt, a.scale, a.causal,
+                       (bf16_t*)a.k_cache, (bf16_t*)a.v_cache, a.slots);
   return hipGetLastError();
 }
 
@@ -571,11 +631,11 @@ static hipError_t launch_paged_d(const PagedArgs& a, hipStream_t stream) {
       };
       const bool one = a.num_decode <= kWave;
       if (a.k_new != nullptr)
-        one ? go(paged_decode_balanced_kernel<D, true, 1>)
-            : go(paged_decode_balanced_kernel<D, true, kBalMaxChunks>);
+        one ? go(paged_decode_balanced_kernel<D, true>)
+            : go(paged_decode_balanced_rows_kernel<D, true>);
       else
-        one ? go(paged_decode_balanced_kernel<D, false, 1>)
-            : go(paged_decode_balanced_kernel<D, false, kBalMaxChunks>);
+        one ? go(paged_decode_balanced_kernel<D, false>)
+            : go(paged_decode_balanced_rows_kernel<D, false>);
     }
     else if (a.k_new != nullptr)
       hipLaunchKernelGGL((paged_decode_kernel<D, true>), dim3((unsigned)grid), dim3(kDecThreads),

@@ -914,7 +914,7 @@ __device__ __forceinline__ void prefill_items(const PfGroup& g, const KV& kv, co
 }
 
 // One query tile (a single item), for the chunked-prefill pieces of the mixed
-// launch.
+// launch and for launches with one tile per workgroup.
 template <int D, int W, class KV>
 __device__ __forceinline__ void prefill_tile_pipe(const PfGroup& g, const KV& kv, int q0,
                                                   bf16_t* __restrict__ s0, bf16_t* __restrict__ s1,
