@@ -147,12 +147,14 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream) -> Optional[int]:
+    # (the raw handle of the current stream: building a Stream object for it
+    # costs about as much as the rest of a call's marshalling)
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
-def _need(t, dtype, name, ndim=None):
+def _refuse(t, dtype, name, ndim):
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if not t.is_cuda:
@@ -163,6 +165,14 @@ def _need(t, dtype, name, ndim=None):
         raise ValueError(f"{name} must be contiguous")
     if ndim is not None and t.dim() != ndim:
         raise ValueError(f"{name} must have {ndim} dimensions")
+
+
+def _need(t, dtype, name, ndim=None):
+    """t is a contiguous GPU tensor of this dtype (and rank): one test in the
+    usual case, the first that fails named otherwise."""
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.is_contiguous()
+            and (ndim is None or t.ndim == ndim)):
+        _refuse(t, dtype, name, ndim)
 
 
 def rag_abi_version() -> int:
