@@ -32,7 +32,8 @@ struct AwqPlan {
   size_t part_bytes;            // the partials of a split over the groups
 };
 
-AwqPlan awq_plan(int M, int N, int K);
+// small: up to 64 rows, the small-batch kernel whatever the layer.
+AwqPlan awq_plan(int M, int N, int K, bool small = false);
 hipError_t launch_awq_gemm(const AwqArgs& a, const AwqPlan& plan, hipStream_t stream);
 
 }  // namespace rag

@@ -82,9 +82,11 @@ rag_status rag_awq_gemm(const void* x, const int32_t* qweight, const void* scale
       !aligned(zeros, 16))
     return fail(RAG_ERR_INVALID_ARG,
                 "awq gemm: x/qweight/scales/zeros/y must be 16-byte aligned");
-  const rag::AwqPlan plan = rag::awq_plan(M, N, K);
+  rag::AwqPlan plan = rag::awq_plan(M, N, K);
   const size_t need = plan.counter_bytes + plan.part_bytes;
-  if (!workspace || workspace_bytes < need)
+  // up to 64 rows the small-batch kernel may do with less
+  if (M <= kTileM && workspace && workspace_bytes < need) plan = rag::awq_plan(M, N, K, true);
+  if (!workspace || workspace_bytes < plan.counter_bytes + plan.part_bytes)
     return fail(RAG_ERR_WORKSPACE, "awq gemm: workspace of %zu bytes needed, %zu given", need,
                 workspace ? workspace_bytes : (size_t)0);
   if (!aligned(workspace, 256))

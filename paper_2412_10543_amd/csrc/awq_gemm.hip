@@ -857,7 +857,7 @@ static double awq_md_cost(const MdTile& c, int64_t tiles, int splits, int groups
   return t;
 }
 
-AwqPlan awq_plan(int M, int N, int K) {
+AwqPlan awq_plan(int M, int N, int K, bool small) {
   AwqPlan p{};
   p.groups = K / kAwqGroup;
   const size_t up = 255;
@@ -869,7 +869,7 @@ AwqPlan awq_plan(int M, int N, int K) {
   // (gate_up at 32 rows 27 against 20, N = 12288 15.7 either way).
   const bool knobs = env_int("RAG_AWQ_SM_NB") > 0 || env_int("RAG_AWQ_SM_SPLITS") > 0;
   const bool wide = (M > 32 && (int64_t)N * K >= (int64_t)4608 * 4096) || (M > 16 && N > 16384);
-  if (M > 64 || (wide && !knobs)) {
+  if (M > 64 || (wide && !knobs && !small)) {
     double best = 0;
     for (const MdTile& c : kMdTiles) {
       if (c.mb > 1 && 32 * c.mb > M) continue;

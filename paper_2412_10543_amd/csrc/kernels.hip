@@ -412,7 +412,9 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
     int units = 0;
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) {
-      un[c] = min((int)ceilf((float)pg[c] * rq), a.slots);
+      // (a thousandth off: a row of just the quota is one piece in spite of
+      // the reciprocal's rounding)
+      un[c] = pg[c] > 0 ? min(max((int)ceilf((float)pg[c] * rq - 1e-3f), 1), a.slots) : 0;
       const int incl = wave_scan_add(un[c]);
       uf[c] = units + incl - un[c];
       units += __builtin_amdgcn_readlane(incl, 63);

@@ -74,3 +74,13 @@ def test_one_workspace_for_every_shape():
         y = _run(p, *dev, ws=ws)
         assert torch.equal(y.view(torch.int16), alone.view(torch.int16)), (M, N, K)
         _check(p, y, rows=[0, M // 2, M - 1], cols=[0, 1, N // 2, N - 1])
+
+
+def test_small_workspace_takes_the_small_batch_kernel():
+    """32 rows of a layer that the row-tiled kernel would split: a call that
+    brings only what the small-batch kernel needs (nothing) still runs."""
+    M, N, K = 32, 16512, 2048
+    assert binding.rag_awq_workspace_size(M, N, K) > 256
+    p = awq_problem(M, N, K, seed=3, device="cuda")
+    ws = torch.zeros(256, dtype=torch.uint8, device="cuda")
+    _check(p, _run(p, *_device(p), ws=ws), cols=list(range(0, N, 31)))
