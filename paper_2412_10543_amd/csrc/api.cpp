@@ -111,8 +111,9 @@ int32_t resolve_splits(int32_t num_decode, int32_t hkv, int32_t max_blocks, int3
 //   Fewer (row, kv head) pairs than CUs: always, as uniform splits leave CUs
 //   idle or unevenly loaded.
 //   More pairs: from tables of kBalWideTable pages on, where rows can differ by
-//   enough to matter (narrower ones: one workgroup per pair, 29.0 us for 64 rows
-//   of 600 tokens against 29.8), with at most kBalManySlots pieces a row.
+//   enough to matter (40 rows of 2k-8k tokens 195 us uniform, 130 balanced),
+//   with at most kBalManySlots pieces a row.  In narrower tables the plan only
+//   costs its time (64 rows of 600 tokens 27.0 us uniform, 28.2 balanced).
 constexpr int32_t kBalWideTable = 128;
 constexpr int32_t kBalManySlots = 8;
 
