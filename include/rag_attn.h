@@ -156,9 +156,10 @@ int32_t rag_attn_decode_num_splits(int32_t num_decode_seqs,
 
 /*
  * Bytes of workspace rag_attn_decode_paged needs for the same arguments (0
- * when the decode rows use a single split).  Layout (library-internal): int32
- * arrival counters [num_decode_seqs, num_kv_heads], fp32 partial outputs
- * [num_decode_seqs, num_q_heads, splits, head_dim] and fp32 partial
+ * when the decode rows use a single split).  Layout (library-internal): 65,536
+ * int32 arrival counters (as many for every call, whatever its rows, so that
+ * calls of different sizes may follow each other in one workspace), fp32 partial
+ * outputs [num_decode_seqs, num_q_heads, splits, head_dim] and fp32 partial
  * log-sum-exp values [num_decode_seqs, num_q_heads, splits].
  */
 size_t rag_attn_decode_workspace_size(int32_t num_decode_seqs,
@@ -192,7 +193,8 @@ size_t rag_attn_decode_workspace_size(int32_t num_decode_seqs,
  *   block_size  must be 16.  head_dim 64 or 128.  The decode rows need
  *            num_q_heads / num_kv_heads <= 16.
  *   num_splits  0 = automatic; else the number of KV splits per decode row
- *            (clamped to [1, min(64, max_blocks_per_seq)]).
+ *            (clamped to [1, min(64, max_blocks_per_seq)]; 1 with more than
+ *            65,536 (decode row, kv head) pairs).
  *            Automatic: about one unit of work per CU.  A pure decode batch
  *            (cu_seqlens_q == NULL) of at most 256 rows is cut on the GPU from
  *            its rows' lengths, so that rows of different lengths still give

@@ -96,7 +96,12 @@ int32_t auto_splits(int32_t num_decode, int32_t hkv, int32_t max_blocks) {
   return (int32_t)std::max<int64_t>(1, n);
 }
 
-int32_t resolve_splits(int32_t num_decode, int32_t hkv, int32_t max_blocks, int32_t requested) {
+// Uniform splits.  counted: none where they would need more arrival counters
+// than a workspace has (so many rows fill the chip unsplit, and the workspace
+// may be small); the static scratch refuses such calls instead.
+int32_t resolve_splits(int32_t num_decode, int32_t hkv, int32_t max_blocks, int32_t requested,
+                       bool counted = true) {
+  if (counted && (int64_t)num_decode * hkv > rag::kDecCounters) return 1;
   int32_t n = requested > 0 ? requested : auto_splits(num_decode, hkv, max_blocks);
   n = std::max(1, std::min({n, std::max(1, max_blocks), kMaxSplits}));
   // No split may be empty for the longest sequence: shrink to ceil(P / pps).
@@ -123,7 +128,9 @@ struct Balanced {
 
 Balanced balanced_plan(int32_t num_decode, int32_t hkv, int32_t max_blocks, int32_t requested) {
   const Balanced none{0, 0};
-  if (requested > 0 || num_decode <= 0 || num_decode > rag::kBalMaxRows) return none;
+  if (requested > 0 || num_decode <= 0 || num_decode > rag::kBalMaxRows ||
+      (int64_t)num_decode * hkv > rag::kDecCounters)
+    return none;
   const bool many = (int64_t)num_decode * hkv >= kTargetUnits;
   if (many && max_blocks < kBalWideTable) return none;
   // no more units than pages / kMinPagesPerUnit (what the kernel uses)
@@ -143,19 +150,19 @@ int32_t decode_slots(int32_t num_decode, int32_t hkv, int32_t max_blocks, int32_
                   balanced_plan(num_decode, hkv, max_blocks, requested).slots);
 }
 
-// Workspace: [arrival counters int32, one per (decode row, kv head)]
-// [partial outputs fp32] [partial log-sum-exp fp32], each 256-byte aligned.
+// Workspace: [kDecCounters arrival counters int32, the first of them used: one
+// per (decode row, kv head)] [partial outputs fp32] [partial log-sum-exp fp32],
+// each 256-byte aligned.
 struct WsLayout {
   size_t o_off, lse_off, bytes;
 };
 
-WsLayout workspace_layout(int32_t num_decode, int32_t hq, int32_t hkv, int32_t d,
-                          int32_t splits) {
+WsLayout workspace_layout(int32_t num_decode, int32_t hq, int32_t d, int32_t splits) {
   WsLayout w{0, 0, 0};
   if (splits <= 1 || num_decode <= 0) return w;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t rows = (size_t)num_decode * hq * splits;
-  w.o_off = up((size_t)num_decode * hkv * sizeof(int32_t));
+  w.o_off = (size_t)rag::kDecCounters * sizeof(int32_t);
   w.lse_off = w.o_off + up(rows * d * sizeof(float));
   w.bytes = w.lse_off + up(rows * sizeof(float));
   return w;
@@ -276,9 +283,9 @@ rag_status decode_paged_impl(const void* q, const void* k_cache, const void* v_c
   if (num_seqs == 0) return ok();
   if (max_blocks_per_seq == 0) return fail(RAG_ERR_INVALID_ARG, "decode: max_blocks_per_seq is 0");
 
-  const int32_t splits =
-      num_decode > 0 ? resolve_splits(num_decode, num_kv_heads, max_blocks_per_seq, num_splits)
-                     : 1;
+  const int32_t splits = num_decode > 0 ? resolve_splits(num_decode, num_kv_heads,
+                                                         max_blocks_per_seq, num_splits, !scratch)
+                                        : 1;
   // (mixed batches are cut uniformly)
   Balanced bal = cu_seqlens_q == nullptr ? balanced_plan(num_decode, num_kv_heads,
                                                          max_blocks_per_seq, num_splits)
@@ -287,7 +294,7 @@ rag_status decode_paged_impl(const void* q, const void* k_cache, const void* v_c
   // the call where the static scratch, or the workspace given, is too small
   // for the balanced plan.
   if (bal.units > 0 && (int64_t)num_decode * num_kv_heads >= kTargetUnits) {
-    const WsLayout b = workspace_layout(num_decode, num_q_heads, num_kv_heads, head_dim,
+    const WsLayout b = workspace_layout(num_decode, num_q_heads, head_dim,
                                         std::max(splits, bal.slots));
     const bool fits =
         scratch ? rag::decode_scratch_fits((size_t)num_decode * num_kv_heads, b.bytes - b.o_off)
@@ -295,7 +302,7 @@ rag_status decode_paged_impl(const void* q, const void* k_cache, const void* v_c
     if (!fits) bal = Balanced{0, 0};
   }
   const int32_t slots = std::max(splits, bal.slots);
-  const WsLayout ws = workspace_layout(num_decode, num_q_heads, num_kv_heads, head_dim, slots);
+  const WsLayout ws = workspace_layout(num_decode, num_q_heads, head_dim, slots);
   const size_t need = ws.bytes;
   if (!scratch && need > 0 && (workspace == nullptr || workspace_bytes < need))
     return fail(RAG_ERR_WORKSPACE, "decode: workspace of %zu bytes needed, %zu given", need,
@@ -421,7 +428,7 @@ size_t rag_attn_decode_workspace_size(int32_t num_decode_seqs, int32_t num_q_hea
     return 0;
   const int32_t n = rag_attn_decode_num_splits(num_decode_seqs, num_kv_heads,
                                                max_blocks_per_seq, block_size, num_splits);
-  return workspace_layout(num_decode_seqs, num_q_heads, num_kv_heads, head_dim, n).bytes;
+  return workspace_layout(num_decode_seqs, num_q_heads, head_dim, n).bytes;
 }
 
 rag_status rag_attn_decode_paged(const void* q, const void* k_cache, const void* v_cache,

@@ -219,6 +219,12 @@ constexpr int kDecThreads = 256;
 constexpr int kDecWaves = kDecThreads / kWave;
 constexpr int kDecMaxGroup = 16;           // q heads per kv head (MFMA N)
 constexpr int kDecMaxSplits = 64;          // pieces of a row that a merge takes (one lane each)
+// Arrival counters of a decode call, one per (row, kv head), at most: the part
+// of a workspace, and of the static scratch, that holds nothing else.  Calls
+// leave it zero, while the partials behind it keep what the last call wrote;
+// were its size the call's own, a call of more rows would find partials where
+// it counts.
+constexpr int kDecCounters = 65536;
 constexpr int kDecMinPages = 16;           // fewest pages a balanced decode unit is cut for
 // Balanced decode: how far above the mean load (in pages) the largest whole
 // piece may be before rows are cut across units instead.  A second piece costs

@@ -16,6 +16,7 @@
 
 #include <mutex>
 
+#include "common.h"
 #include "errors.h"
 #include "launch.h"
 
@@ -27,7 +28,7 @@ namespace rag {
 
 namespace {
 
-constexpr size_t kScratchCounters = 65536;
+constexpr size_t kScratchCounters = kDecCounters;
 constexpr size_t kCounterBytes = kScratchCounters * sizeof(int);
 constexpr int kMaxDevices = 64;
 

@@ -1,0 +1,80 @@
+"""Calls of different sizes following each other in one workspace that was
+zero-filled once: what one call leaves behind the counters must never lie where
+another counts.  Each result equals, bit for bit, that of a workspace of its own."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_support import scale_for, to_dev_i32, workspace_for
+from paper_2412_10543_amd import binding
+from paper_2412_10543_amd.workloads import normal_bf16, paged_pool
+
+
+def _up(x):
+    return (x + 255) // 256 * 256
+
+
+def test_decode_counters_keep_their_place():
+    """The bytes in front of the partials are the same for every call, and
+    enough for its counters."""
+    hq, d = 32, 128
+    front = set()
+    for rows, hkv, mb, splits in [(1, 8, 400, 0), (31, 8, 400, 0), (32, 8, 400, 0), (40, 8, 400, 0),
+                                  (256, 8, 400, 0), (20, 8, 40, 0), (3, 8, 188, 6), (300, 8, 40, 2),
+                                  (1100, 1, 313, 4), (8192, 8, 313, 2), (200, 1, 563, 0)]:
+        n = binding.rag_attn_decode_num_splits(rows, hkv, mb, 16, splits)
+        assert n > 1
+        size = binding.rag_attn_decode_workspace_size(rows, hq, hkv, d, mb, 16, splits)
+        front.add(size - _up(rows * hq * n * d * 4) - _up(rows * hq * n * 4))
+        assert min(front) >= 4 * rows * hkv
+    assert len(front) == 1
+    # more pairs than there are counters: not split
+    assert binding.rag_attn_decode_num_splits(8193, 8, 313, 16, 2) == 1
+    assert binding.rag_attn_decode_workspace_size(8193, hq, 8, d, 313, 16, 2) == 0
+
+
+def _decode(q, pool, lens, hkv, table, ws, splits, cu, nd):
+    o = torch.full_like(q, float("nan"))
+    kw = {} if cu is None else dict(cu_seqlens_q=to_dev_i32(cu), num_decode_seqs=nd,
+                                    max_seqlen_q=max(np.diff(cu)))
+    binding.rag_attn_decode_paged(q, pool.k_cache, pool.v_cache, o, table, to_dev_i32(lens),
+                                  scale_for(q.shape[2]), num_splits=splits, workspace=ws, **kw)
+    torch.cuda.synchronize()
+    return o
+
+
+@pytest.mark.gpu
+def test_decode_batches_grow_and_shrink_in_one_workspace():
+    """Rows that differ from call to call, on both sides of 256 (row, kv head)
+    pairs, automatic and explicit splits, and a mixed batch."""
+    hq, hkv, d, mb = 32, 8, 64, 400
+    r = np.random.Generator(np.random.PCG64(31))
+    lens = [int(x) for x in r.integers(4500, 16 * mb, size=64)]
+    pool = paged_pool(lens, hkv, d, 32, device="cuda", max_blocks=mb)
+    calls = [(31, 0, 0), (40, 0, 0), (20, 0, 0), (64, 0, 0), (31, 0, 0), (7, 5, 0), (64, 3, 0),
+             (30, 0, 2), (50, 2, 0), (33, 4, 3), (64, 0, 0)]
+    size = max(binding.rag_attn_decode_workspace_size(n, hq, hkv, d, mb, 16, s) for n, s, _ in calls)
+    ws = torch.zeros(size, dtype=torch.uint8, device="cuda")
+    for i, (n, splits, pieces) in enumerate(calls):
+        print(f"call {i}: {n} rows, splits {splits}, {pieces} pieces", flush=True)
+        cu = None if pieces == 0 else list(range(n + 1)) + [n + 24 * (j + 1) for j in range(pieces)]
+        s = n + pieces
+        q = normal_bf16((n if cu is None else cu[-1], hq, d), 40 + i, "cuda")
+        table = pool.block_tables[:s].contiguous()
+        own = workspace_for(n, hq, hkv, d, mb, splits)
+        want = _decode(q, pool, lens[:s], hkv, table, own, splits, cu, n)
+        got = _decode(q, pool, lens[:s], hkv, table, ws, splits, cu, n)
+        assert bool(torch.isfinite(got).all()), f"call {i}: rows left unwritten"
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)), f"call {i}"
+
+
+@pytest.mark.gpu
+def test_more_rows_than_counters_are_not_split():
+    rows, hq, hkv, d = 8200, 8, 8, 64
+    lens = [1 + (7 * i) % 40 for i in range(rows)]
+    pool = paged_pool(lens, hkv, d, 51, device="cuda")
+    q = normal_bf16((rows, hq, d), 52, "cuda")
+    one = _decode(q, pool, lens, hkv, pool.block_tables, None, 1, None, rows)
+    two = _decode(q, pool, lens, hkv, pool.block_tables, None, 2, None, rows)
+    assert torch.equal(one.view(torch.int16), two.view(torch.int16))
+    assert bool(torch.isfinite(two).all())
