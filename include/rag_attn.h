@@ -200,8 +200,8 @@ size_t rag_attn_decode_workspace_size(int32_t num_decode_seqs,
  *            its rows' lengths, so that rows of different lengths still give
  *            every CU about the same amount to read, when it has fewer (row, kv
  *            head) pairs than CUs, or a block table of at least 128 blocks
- *            (and the workspace that takes); otherwise every row is cut into
- *            the same number of splits.
+ *            (and the workspace that takes) and rows that differ enough;
+ *            otherwise every row is cut into the same number of splits.
  *            Pieces of a row are merged (log-sum-exp) inside the same kernel
  *            by the last one to finish.
  *   workspace, workspace_bytes  device scratch of at least

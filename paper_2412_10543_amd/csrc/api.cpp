@@ -82,7 +82,7 @@ constexpr int32_t kMaxGroupDecode = 16;
 // unit per CU, cap a unit at 512 pages (load balance across sequences of very
 // different length) and keep at least 16 pages per unit (two steps per
 // wave).  The in-kernel merge handles at most 64 splits.
-constexpr int32_t kTargetUnits = 256;
+constexpr int32_t kTargetUnits = rag::kDecUnits;
 constexpr int32_t kMaxPagesPerUnit = 512;
 constexpr int32_t kMinPagesPerUnit = 16;
 constexpr int32_t kMaxSplits = rag::kDecMaxSplits;
@@ -116,9 +116,10 @@ int32_t resolve_splits(int32_t num_decode, int32_t hkv, int32_t max_blocks, int3
 //   Fewer (row, kv head) pairs than CUs: always, as uniform splits leave CUs
 //   idle or unevenly loaded.
 //   More pairs: from tables of kBalWideTable pages on, where rows can differ by
-//   enough to matter (40 rows of 2k-8k tokens 195 us uniform, 130 balanced),
-//   with at most kBalManySlots pieces a row.  In narrower tables the plan only
-//   costs its time (64 rows of 600 tokens 27.0 us uniform, 28.2 balanced).
+//   enough to matter, with at most kBalManySlots pieces a row; whether they do
+//   the kernel finds from the lengths, and leaves them whole otherwise (as fast
+//   as here: 32 rows of 100-200 keys 7.9 us, uniform splits 8.1; 64 of 600 28.1
+//   and 28.2; 250 of 100-200 33.9 and 33.7).
 constexpr int32_t kBalWideTable = 128;
 constexpr int32_t kBalManySlots = 8;
 

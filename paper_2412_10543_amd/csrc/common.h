@@ -225,6 +225,7 @@ constexpr int kDecMaxSplits = 64;          // pieces of a row that a merge takes
 // were its size the call's own, a call of more rows would find partials where
 // it counts.
 constexpr int kDecCounters = 65536;
+constexpr int kDecUnits = 256;             // decode units aimed at, about one per CU
 constexpr int kDecMinPages = 16;           // fewest pages a balanced decode unit is cut for
 // Balanced decode: how far above the mean load (in pages) the largest whole
 // piece may be before rows are cut across units instead.  A second piece costs

@@ -49,16 +49,17 @@ struct DecodeOut {
 // the same launch, see decode_unit).
 template <int D, int NP, bool kAppend = false>
 __device__ __forceinline__ void decode_wave(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
-    size_t block_stride, const int32_t* __restrict__ table, int kv_len, int group,
-    int p_first, int p_end, int p_stride, float scale, bf16_t* __restrict__ vt,
+    int tid, const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
+    const bf16_t* __restrict__ vc, size_t block_stride, const int32_t* __restrict__ table,
+    int kv_len, int group, int p_first, int p_end, int p_stride, float scale,
+    bf16_t* __restrict__ vt,
     f32x4 (&oacc)[D / 16], float& m_used, float& l, const bf16_t* __restrict__ k_new = nullptr,
     const bf16_t* __restrict__ v_new = nullptr) {
   static_assert(NP % 2 == 0, "pages are consumed in pairs (32 keys per MFMA)");
   using L = DecLds<D, NP>;
   constexpr int kKs = D / 32;   // k-steps over d for S^T
   constexpr int kDt = D / 16;   // 16-row d tiles of O^T
-  const int lane = threadIdx.x & 63;
+  const int lane = tid & 63;
   const int l16 = lane & 15, gq = lane >> 4;
 
   // Q^T fragments: lane holds head l16, d = 32*ks + 8*gq .. +8.  Lanes past the
@@ -226,10 +227,10 @@ __device__ __forceinline__ void decode_wave(
 // and most rows have at most 8 splits.  (The mixed launch's eight-wave units
 // keep 16: 1714 us against 1735 with 8 on 256 rows and four pieces.)
 template <int D, int W>
-__device__ __forceinline__ void merge_splits(const DecodeOut& out, int group) {
+__device__ __forceinline__ void merge_splits(int tid, const DecodeOut& out, int group) {
   constexpr int kPer = D / 64;                 // 2 (D = 128) or 1 (D = 64)
   constexpr int kBatch = W > 4 ? 16 : 8;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = tid & 63, wave = tid >> 6;
   for (int h = wave; h < group; h += W) {
     const float* pl = out.part_lse + (size_t)h * out.num_splits;
     const float* po = out.part_o + (size_t)h * out.num_splits * D + lane * kPer;
@@ -278,24 +279,25 @@ constexpr int dec_merge_bytes() {
   return (W * 16 * D + 2 * W * 16 + 1) * 4;
 }
 
-// The whole unit: the workgroup's W waves cover the page range
-// [p_begin, p_end) in interleaved steps of NP pages, merge through LDS and
-// write either the final rows (n_sp == 1) or this split's partial rows; the
-// last split of the row to arrive then merges all partials.
+// The whole unit (tid: the thread's index in the workgroup): the W waves cover
+// the page range [p_begin, p_end) in interleaved steps of NP pages, merge
+// through LDS and write either the final rows (n_sp == 1) or this split's
+// partial rows; the last split of the row to arrive then merges all partials.
 //
 // kAppend: the unit whose range holds the last page also stores the new
 // token's K and V rows (k_new, v_new) into its cache slot, key kv_len - 1 of
 // the block table.  No unit of this launch reads that slot from the cache.
 template <int D, int NP, int W, bool kAppend = false>
 __device__ __forceinline__ void decode_unit(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
-    size_t block_stride, const int32_t* __restrict__ table, int kv_len, int group,
-    int p_begin, int p_end, float scale, const DecodeOut& out, bf16_t* __restrict__ lds,
+    int tid, const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
+    const bf16_t* __restrict__ vc, size_t block_stride, const int32_t* __restrict__ table,
+    int kv_len, int group, int p_begin, int p_end, float scale, const DecodeOut& out,
+    bf16_t* __restrict__ lds,
     const bf16_t* __restrict__ k_new = nullptr, const bf16_t* __restrict__ v_new = nullptr) {
   using L = DecLds<D, NP, W>;
   static_assert(dec_merge_bytes<D, W>() <= L::kBytes, "merge area must fit in the V slices");
   constexpr int kDt = D / 16;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = tid >> 6, lane = tid & 63;
   const int l16 = lane & 15, gq = lane >> 4;
 
   // The new token's rows and their slot are requested before the pages and
@@ -310,7 +312,7 @@ __device__ __forceinline__ void decode_unit(
   }
   f32x4 oacc[kDt];
   float m_used, l;
-  decode_wave<D, NP, kAppend>(q, kc, vc, block_stride, table, kv_len, group,
+  decode_wave<D, NP, kAppend>(tid, q, kc, vc, block_stride, table, kv_len, group,
                               p_begin + wave * NP, p_end, W * NP, scale,
                               lds + wave * L::kElemsWave, oacc, m_used, l, k_new, v_new);
 
@@ -382,12 +384,12 @@ __device__ __forceinline__ void decode_unit(
   wait_all_memory();
   __syncthreads();
   int* flag = reinterpret_cast<int*>(ml + W * 16);
-  if (threadIdx.x == 0)
+  if (tid == 0)
     *flag = __hip_atomic_fetch_add(out.arrival, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if (*flag != out.n_sp - 1) return;
-  merge_splits<D, W>(out, group);
-  if (threadIdx.x == 0)
+  merge_splits<D, W>(tid, out, group);
+  if (tid == 0)
     __hip_atomic_store(out.arrival, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 

@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstdlib>
+#include <type_traits>
 
 #include "common.h"
 #include "decode_unit.h"
@@ -291,7 +292,7 @@ struct PagedKernelArgs {
 // One piece of a decode row: pages [p_begin, p_end) of (row s, kv head kvh),
 // split sp of n_sp, on W waves taking NP pages a step.
 template <int D, int NP, int W, bool kAppend = false>
-__device__ __forceinline__ void decode_piece(const PagedKernelArgs& a, int group,
+__device__ __forceinline__ void decode_piece(int tid, const PagedKernelArgs& a, int group,
                                              size_t block_stride, int s, int kvh, int kv_len,
                                              int p_begin, int p_end, int sp, int n_sp,
                                              bf16_t* lds) {
@@ -306,7 +307,7 @@ __device__ __forceinline__ void decode_piece(const PagedKernelArgs& a, int group
   out.n_sp = n_sp;
   out.num_splits = a.slots;
   const size_t nrow = ((size_t)s * a.hkv + kvh) * D;
-  decode_unit<D, NP, W, kAppend>(a.q + head * D, a.kc + (size_t)kvh * 16 * D,
+  decode_unit<D, NP, W, kAppend>(tid, a.q + head * D, a.kc + (size_t)kvh * 16 * D,
                                  a.vc + (size_t)kvh * 16 * D, block_stride,
                                  a.tables + (size_t)s * a.max_blocks, kv_len, group, p_begin,
                                  p_end, a.scale, out, lds, kAppend ? a.k_new + nrow : nullptr,
@@ -328,14 +329,16 @@ __device__ __forceinline__ void decode_block(const PagedKernelArgs& a, int u, in
   if (sp >= n_sp && sp > 0) return;
   const int p_begin = sp * a.pps;
   const int p_end = min(n_pages, p_begin + a.pps);
-  decode_piece<D, NP, W, kAppend>(a, group, block_stride, s, kvh, kv_len, p_begin, p_end, sp,
-                                  n_sp, lds);
+  decode_piece<D, NP, W, kAppend>(threadIdx.x, a, group, block_stride, s, kvh, kv_len, p_begin,
+                                  p_end, sp, n_sp, lds);
 }
 
 // Balanced decode units: a pure decode batch is cut into units from the rows'
 // actual lengths, bal_units of them per kv head where that is more than the
-// rows, else at most rows + bal_units.  Two plans, each giving row s the un
-// consecutive units from uf on:
+// rows, else at most rows + bal_units.  With as many (row, kv head) pairs as CUs
+// (kFull) rows that are short or alike stay whole, one unit each (bal_skewed).
+// Otherwise one of two plans, each giving row s the un consecutive units from uf
+// on:
 //   whole pieces   every row is cut on its own into equal pieces of at most
 //                  about a quota of pages, the smallest quota tried for which
 //                  the pieces fit the units: one piece per unit;
@@ -348,10 +351,9 @@ __device__ __forceinline__ void decode_block(const PagedKernelArgs& a, int u, in
 // (one lane per row, prefix sums over the lanes; kChunks chunks of 64 rows) and
 // short in code: walked row by row with integer divisions it took 3 us of that
 // launch, now 0.7.
-// Measured (7B heads, graph-replayed, before -> now): 20 rows x 600 tokens 20.3
-// -> 13.8 us, 16 x 576-1088 21.4 -> 16.6, 8 x 2.6k-10k 47.6 -> 43.3, 16 x
-// 2.6k-10k 75.1 -> 72.9, 40 x 2k-8k 195 -> 129; 255 rows x 100-900 with one kv
-// head 85 -> 18.
+// Measured (7B heads, graph-replayed, walked and always crossing -> now): 20 rows
+// x 600 tokens 20.3 -> 13.8 us, 16 x 576-1088 21.4 -> 16.6, 8 x 2.6k-10k 47.6 ->
+// 43.3, 16 x 2.6k-10k 75.1 -> 72.9; 255 rows x 100-900 with one kv head 85 -> 18.
 
 // Inclusive prefix sum over the wave's lanes.
 __device__ __forceinline__ int wave_scan_add(int x) {
@@ -364,9 +366,46 @@ __device__ __forceinline__ int wave_scan_add(int x) {
   return x;
 }
 
-template <int D, int NP, int W, bool kAppend, int kChunks>
+// Inclusive prefix maximum of values from 0 on.
+__device__ __forceinline__ int wave_scan_max(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return x;
+}
+
+// Pages (see bal_skewed).
+template <int D>
+constexpr float kBalOver = D == 64 ? 112.f : 56.f;
+template <int D>
+constexpr float kBalShort = D == 64 ? 45.f : 32.f;
+
+// With as many (row, kv head) pairs as CUs or more: whether the rows' pages
+// differ by enough for a plan to be worth it.  `over`: how many more pages the
+// busiest CU has with whole rows, one workgroup each, than with an even cut.
+// Fitted to 470 timed batches of 256-2000 pairs (32 to 9000 keys a row, ten head
+// shapes): within 0.3% of the better of plan and whole rows on average, where
+// always a plan is up to 1.4 times slower than whole rows (128 rows x 1200-1500
+// keys, 2 kv heads: 33.4 us whole, 46.3 cut) and whole rows always up to 2.8
+// times than a plan (32 x 100-200 keys and one of 4000, 8 kv heads: 44.0 whole,
+// 15.9 cut).  40 x 2k-8k: 176 whole, 128 cut.
+template <int D>
+__device__ __forceinline__ bool bal_skewed(int rows, int units, int total, int longest, int group) {
+  const float mean = (float)total * __builtin_amdgcn_rcpf((float)rows);
+  const float even = (float)total * __builtin_amdgcn_rcpf((float)units);
+  const float worst = (float)longest + mean * (float)((rows - 1) / units);
+  const float over = worst - even;
+  return over > kBalOver<D> * (1.f + 0.0625f * (float)group) ||
+         (over > kBalShort<D> && worst > 2.f * even);
+}
+
+template <int D, int NP, int W, bool kAppend, int kChunks, bool kFull>
 __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, int u, int group,
-                                                      size_t block_stride, bf16_t* lds) {
+                                                      size_t block_stride, bf16_t* lds,
+                                                      int* keys) {
   const int kvh = u % a.hkv, k = u / a.hkv;
   const int S = a.num_decode, lane = threadIdx.x & 63, cap = a.max_blocks * 16;
   // per lane, rows 64 c + lane: keys, pages, first global page, units
@@ -377,24 +416,49 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
     kl[c] = min(a.kv_lens[min(s, S - 1)], cap);
     if (s >= S) kl[c] = 0;
   }
-  int total = 0;
 #pragma unroll
-  for (int c = 0; c < kChunks; ++c) {
-    pg[c] = (kl[c] + 15) >> 4;
-    const int incl = wave_scan_add(pg[c]);
-    st[c] = total + incl - pg[c];
-    total += __builtin_amdgcn_readlane(incl, 63);
+  for (int c = 0; c < kChunks; ++c) pg[c] = (kl[c] + 15) >> 4;
+  bool uncut = false;                        // every row whole: unit k is row k
+  if constexpr (kFull) {                     // (`over` is at most the longest row)
+    uint64_t long_rows = 0;
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c)
+      long_rows |= __builtin_amdgcn_ballot_w64(pg[c] > (int)kBalShort<D>);
+    uncut = long_rows == 0;
+  }
+  int total = 0, longest = 0;
+  auto longest_row = [&] {
+    int m = pg[0];
+#pragma unroll
+    for (int c = 1; c < kChunks; ++c) m = max(m, pg[c]);
+    return (int)__builtin_amdgcn_readlane(wave_scan_max(m), 63);
+  };
+  if (!uncut) {
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      const int incl = wave_scan_add(pg[c]);
+      st[c] = total + incl - pg[c];
+      total += __builtin_amdgcn_readlane(incl, 63);
+    }
+    if constexpr (kFull) {
+      longest = longest_row();
+      uncut = !bal_skewed<D>(S, a.bal_units, total, longest, group);
+    }
+  }
+  if (kFull && uncut) {
+    // (a second copy of the unit's code: through the plans' loop below, these
+    // rows, short as a rule, took 0.4-0.7 us longer)
+    if (k >= S) return;
+    const int kls = min(a.kv_lens[k], cap);
+    decode_piece<D, NP, W, kAppend>(threadIdx.x, a, group, block_stride, k, kvh, kls, 0,
+                                    (kls + 15) >> 4, 0, 1, lds);
+    return;
   }
   // Pages per unit below which the longest row could have more pieces than the
   // workspace has slots for (a crossing row also starts and ends inside one).
   float q_min = (float)kDecMinPages;
   if (a.bal_units > a.slots) {
-    int longest = pg[0];
-#pragma unroll
-    for (int c = 1; c < kChunks; ++c) longest = max(longest, pg[c]);
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) longest = max(longest, __shfl_xor(longest, m, kWave));
-    longest = __builtin_amdgcn_readfirstlane(longest);
+    if constexpr (!kFull) longest = longest_row();
     q_min = fmaxf(q_min, (float)longest * __builtin_amdgcn_rcpf((float)(a.slots - 2)) + 2.f);
   }
   // Whole pieces: quotas from the larger of q_min and the mean per unit on, up
@@ -443,6 +507,9 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
     }
   };
   int lo, hi, s;                             // this unit's global pages and first row
+  uint32_t T = 0, K = 0;                     // crossing: all pages, units
+  // unit holding global page g: ceil((g + 1) K / T) - 1
+  auto unit_of = [&](int g) { return (int)(((uint32_t)(g + 1) * K + T - 1) / T) - 1; };
   if (whole) {
     s = first_row([&](int c) { return k < uf[c] + un[c]; });
     if (s < 0) return;
@@ -453,48 +520,77 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
   } else {
     // at least q_min pages per unit; 32-bit arithmetic: the host takes this
     // path only when rows x table width x units stays below 2^31
-    const uint32_t T = (uint32_t)total;
-    const uint32_t K =
-        max(1u, min((uint32_t)a.bal_units, (uint32_t)((float)total * __builtin_amdgcn_rcpf(q_min))));
+    T = (uint32_t)total;
+    K = max(1u, min((uint32_t)a.bal_units, (uint32_t)((float)total * __builtin_amdgcn_rcpf(q_min))));
     if ((uint32_t)k >= K) return;
     lo = (int)((uint32_t)k * T / K);
     hi = (int)((uint32_t)(k + 1) * T / K);
-    // unit holding global page g: ceil((g + 1) K / T) - 1
-    auto unit_of = [&](int g) { return (int)(((uint32_t)(g + 1) * K + T - 1) / T) - 1; };
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) {
       uf[c] = unit_of(st[c]);
       un[c] = unit_of(st[c] + max(pg[c], 1) - 1) - uf[c] + 1;
     }
     s = first_row([&](int c) { return st[c] + pg[c] > lo; });
-  }
-  // one call site of decode_piece: the kernel's code stays one copy of the unit
-  for (bool first = true;; first = false) {
-    const int gs = row(st, s), ps = row(pg, s);
-    if (gs >= hi) break;
-    if (ps > 0) {
-      if (!first) __syncthreads();           // LDS of the previous piece fully read
-      decode_piece<D, NP, W, kAppend>(a, group, block_stride, s, kvh, row(kl, s),
-                                      max(lo, gs) - gs, min(hi, gs + ps) - gs, k - row(uf, s),
-                                      row(un, s), lds);
+    if constexpr (kFull) {
+      // (every wave writes the same lengths, and reads what it wrote)
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) keys[c * kWave + lane] = kl[c];
     }
-    if (++s >= S) break;
+  }
+  // one call site of decode_piece: the plans' code stays one copy of the unit
+  if constexpr (kFull) {
+    // What is kept per lane, or formed from the thread's index, would sit in
+    // registers through the page loop of a kernel that has none to spare.
+    int gs = row(st, s), ps = row(pg, s), kls = row(kl, s);
+    int ufs = row(uf, s), uns = row(un, s);
+    for (bool first = true;; first = false) {
+      if (ps > 0) {
+        if (!first) __syncthreads();         // LDS of the previous piece fully read
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        decode_piece<D, NP, W, kAppend>(tid & (kDecThreads - 1), a, group, block_stride, s, kvh,
+                                        kls, max(lo, gs) - gs, min(hi, gs + ps) - gs, k - ufs, uns,
+                                        lds);
+      }
+      gs += ps;
+      if (++s >= S || gs >= hi) break;
+      kls = __builtin_amdgcn_readfirstlane(keys[s]);
+      ps = (kls + 15) >> 4;
+      ufs = unit_of(gs);
+      uns = unit_of(gs + max(ps, 1) - 1) - ufs + 1;
+    }
+  } else {
+    for (bool first = true;; first = false) {
+      const int gs = row(st, s), ps = row(pg, s);
+      if (gs >= hi) break;
+      if (ps > 0) {
+        if (!first) __syncthreads();         // LDS of the previous piece fully read
+        decode_piece<D, NP, W, kAppend>(threadIdx.x, a, group, block_stride, s, kvh, row(kl, s),
+                                        max(lo, gs) - gs, min(hi, gs + ps) - gs, k - row(uf, s),
+                                        row(un, s), lds);
+      }
+      if (++s >= S) break;
+    }
   }
 }
 
-// Up to 64 rows, and up to kBalMaxRows.
-template <int D, bool kAppend>
-__global__ __launch_bounds__(kDecThreads, 2) void paged_decode_balanced_kernel(PagedKernelArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16_t lds[DecLds<D>::kBytes / 2];
-  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, 1>(
-      a, blockIdx.x, a.hq / a.hkv, (size_t)a.hkv * 16 * D, lds);
+// Waves per SIMD of a kernel that may leave rows whole: those of the kernel that
+// always does (paged_decode_kernel; with one fewer 250 rows x 100-200 keys took
+// 39.9 us against 33.5, now 34.5).
+template <int D, bool kAppend, bool kFull>
+constexpr int bal_wgs() {
+  return kFull ? (D == 64 ? 3 : 2) + (kAppend ? 0 : 1) : 2;
 }
 
-template <int D, bool kAppend>
-__global__ __launch_bounds__(kDecThreads, 2) void paged_decode_balanced_rows_kernel(PagedKernelArgs a) {
+// kChunks: 1 up to 64 rows, kBalMaxChunks up to kBalMaxRows.  kFull: as many
+// (row, kv head) pairs as CUs, or more.
+template <int D, bool kAppend, int kChunks, bool kFull>
+__global__ __launch_bounds__(kDecThreads, (bal_wgs<D, kAppend, kFull>())) void
+paged_decode_balanced_kernel(PagedKernelArgs a) {
   __shared__ __attribute__((aligned(16))) bf16_t lds[DecLds<D>::kBytes / 2];
-  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, kBalMaxChunks>(
-      a, blockIdx.x, a.hq / a.hkv, (size_t)a.hkv * 16 * D, lds);
+  __shared__ int keys[kFull ? kChunks * kWave : 1];
+  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, kChunks, kFull>(
+      a, blockIdx.x, a.hq / a.hkv, (size_t)a.hkv * 16 * D, lds, keys);
 }
 
 // Decode rows only: one four-wave workgroup per decode unit.  kAppend: each
@@ -628,16 +724,26 @@ static hipError_t launch_paged_d(const PagedArgs& a, hipStream_t stream) {
       hipLaunchKernelGGL(mixed_kernel<D>, dim3((unsigned)grid), dim3(64 * kPfWavesDense), 0,
                          stream, k);
     else if (k.bal_units > 0) {
-      auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kDecThreads), 0, stream, k);
+      // Up to four workgroups a CU: one fewer resident than the non-appending
+      // kernels' registers allow, so that the last ones go where there is room
+      // (36 rows x 157-1256 keys, 16 kv heads: 42 us with two a CU, 49 with three).
+      constexpr int kSpareLds = D == 128 ? 18 << 10 : 21 << 10;
+      auto go = [&](auto append, auto chunks, auto full) {
+        hipLaunchKernelGGL((paged_decode_balanced_kernel<D, append.value, chunks.value,
+                                                         full.value>),
+                           dim3((unsigned)grid), dim3(kDecThreads),
+                           full.value && !append.value && grid <= 4 * kDecUnits ? kSpareLds : 0,
+                           stream, k);
       };
-      const bool one = a.num_decode <= kWave;
-      if (a.k_new != nullptr)
-        one ? go(paged_decode_balanced_kernel<D, true>)
-            : go(paged_decode_balanced_rows_kernel<D, true>);
-      else
-        one ? go(paged_decode_balanced_kernel<D, false>)
-            : go(paged_decode_balanced_rows_kernel<D, false>);
+      auto rows = [&](auto append, auto chunks) {
+        (int64_t)a.num_decode * a.hkv >= kDecUnits ? go(append, chunks, std::true_type())
+                                                   : go(append, chunks, std::false_type());
+      };
+      auto appending = [&](auto append) {
+        a.num_decode <= kWave ? rows(append, std::integral_constant<int, 1>())
+                              : rows(append, std::integral_constant<int, kBalMaxChunks>());
+      };
+      a.k_new != nullptr ? appending(std::true_type()) : appending(std::false_type());
     }
     else if (a.k_new != nullptr)
       hipLaunchKernelGGL((paged_decode_kernel<D, true>), dim3((unsigned)grid), dim3(kDecThreads),

@@ -112,3 +112,50 @@ def test_append_stores_after_the_pages(rows, hq, hkv, d, kind):
     assert torch.equal(o.view(torch.int16), o2.view(torch.int16))
     assert torch.equal(pool.k_cache.view(torch.int16), k2.view(torch.int16))
     assert torch.equal(pool.v_cache.view(torch.int16), v2.view(torch.int16))
+
+
+def _mixed_lens(kind, rows):
+    r = np.random.Generator(np.random.PCG64(7 * rows))
+    if kind == "short":                    # nothing to even out
+        return [int(x) for x in r.integers(1, 300, size=rows)]
+    if kind == "alike":                    # long, but every row about the same
+        return [int(x) for x in r.integers(4990, 5049, size=rows)]
+    return [int(x) for x in r.integers(1, 60, size=rows - 1)] + [6000]     # one long
+
+
+@pytest.mark.parametrize("append", [False, True])
+@pytest.mark.parametrize("rows,hq,hkv,d", [
+    (16, 16, 16, 128), (32, 32, 8, 128), (63, 8, 8, 64), (64, 16, 4, 64), (65, 8, 4, 128),
+    (128, 32, 2, 128), (256, 4, 1, 64), (8, 32, 32, 128), (12, 24, 24, 64)])
+@pytest.mark.parametrize("kind", ["short", "alike", "long"])
+def test_rows_behind_a_wide_table(orc, kind, rows, hq, hkv, d, append):
+    """As many (row, kv head) pairs as CUs and a table wide enough for the plan:
+    rows that are short stay whole (the bits of num_splits=1), long ones that are
+    alike too where they come to about a whole number per CU, and one row that is
+    far longer than the rest is cut."""
+    lens = _mixed_lens(kind, rows)
+    mb = 400
+    assert binding.rag_attn_decode_num_splits(rows, hkv, mb, 16) > 1
+    pool = paged_pool(lens, hkv, d, 960 + rows, device="cuda", max_blocks=mb)
+    q = normal_bf16((rows, hq, d), 961, "cuda")
+    scale, kl = scale_for(d), to_dev_i32(lens)
+    ws = workspace_for(rows, hq, hkv, d, mb)
+
+    def call(**kw):
+        o = torch.full_like(q, float("nan"))
+        if append:
+            kn, vn = (normal_bf16((rows, hkv, d), s, "cuda") for s in (962, 963))
+            binding.rag_attn_decode_paged_append(q, kn, vn, pool.k_cache, pool.v_cache, o,
+                                                 pool.block_tables, kl, scale, **kw)
+        else:
+            binding.rag_attn_decode_paged(q, pool.k_cache, pool.v_cache, o, pool.block_tables, kl,
+                                          scale, **kw)
+        torch.cuda.synchronize()
+        return o
+
+    got, again, whole = call(workspace=ws), call(workspace=ws), call(num_splits=1)
+    assert torch.equal(got.view(torch.int16), again.view(torch.int16))
+    uncut = kind == "short" or (kind == "alike" and -rows * hkv % 256 < 32)
+    assert torch.equal(got.view(torch.int16), whole.view(torch.int16)) == uncut
+    # (the appended rows are in the cache by now)
+    assert_parity(got, oracle_paged(orc, q, pool, scale), f"{kind} {rows} rows")
