@@ -467,11 +467,12 @@ rag_status rag_awq_pack_weights(const uint8_t *q, int32_t K, int32_t N,
                                 int32_t group_size, int32_t *packed);
 
 /* Bytes of workspace rag_awq_gemm needs (0 for M == 0, invalid shapes, or
- * a small batch that needs none).  Library-internal layout: arrival counters,
- * then fp32 partial outputs where the weight groups are split over workgroups
- * (few output tiles or column blocks, or a long K in a small batch).  M > 64:
- * K / 128 * M * 16 bytes (rounded up to 256), then whole planes of M * N * 4
- * bytes.  Partials are added in a fixed order, so results do not depend on
+ * a small batch that needs none).  Library-internal layout: 16,384 int32
+ * arrival counters (as many for every call), then fp32 partial outputs where the
+ * weight groups are split over workgroups (few output tiles or column blocks, or
+ * a long K in a small batch).  M > 64: the larger of those counters and K / 128 *
+ * M * 16 bytes (rounded up to 256), then whole planes of M * N * 4 bytes.
+ * Partials are added in a fixed order, so results do not depend on
  * timing.  For M <= 64 the environment variables RAG_AWQ_SM_NB (16-column
  * blocks per workgroup: 1, 2, 4 or 8) and RAG_AWQ_SM_SPLITS (at least this many
  * splits) take the small-batch kernel and override its choice, read at each
@@ -489,8 +490,9 @@ size_t rag_awq_workspace_size(int32_t M, int32_t N, int32_t K,
  *   workspace  device, >= rag_awq_workspace_size(M, N, K, group_size) bytes,
  *            256-byte aligned, zero-filled once before its first use: it
  *            starts with the arrival counters of a split over the weight
- *            groups, which every call leaves at zero again.  Overlapping
- *            calls must not share it.
+ *            groups, which every call leaves at zero again.  Calls of any
+ *            layers and batches may follow each other in it; overlapping calls
+ *            must not share it.
  * Returns RAG_OK (M == 0 is a no-op; x and y may then be NULL),
  * RAG_ERR_INVALID_ARG (null pointer, a pointer not 16-byte aligned, negative
  * M, N or K not positive), RAG_ERR_UNSUPPORTED (group_size not 128, K or N not a multiple of

@@ -35,6 +35,12 @@ namespace rag {
 
 constexpr int kAwqGroup = 128;
 constexpr int kAwqCus = 256;     // MI355X compute units
+// Arrival counters at a workspace's start, one per column block or output tile
+// of a split launch, at most: the same bytes for every call, as the partials
+// behind them keep what the last call wrote and calls of any layer and batch
+// may follow each other in one workspace.
+constexpr int kAwqCounters = 16384;
+constexpr size_t kAwqCounterBytes = kAwqCounters * sizeof(int);
 
 // A value the compiler must keep in a VGPR (no constant folding).
 __device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
@@ -160,8 +166,7 @@ __device__ __forceinline__ ColScale col_scale_plain(uint32_t sb, uint32_t z) {
 namespace awq_md {
 constexpr int kGroupM = 8;                       // M tiles per raster group
 constexpr int kOutStride = 144;                  // bytes per row of the output transpose
-constexpr size_t kMinCounters = 1280;            // counter bytes at a workspace's start
-constexpr int kMaxSplitTiles = (int)(kMinCounters / sizeof(int));
+constexpr int kMaxSplitTiles = 320;              // (more tiles fill the chip unsplit)
 template <int MB, int NW>
 struct Shape {
   static constexpr int kBM = 32 * MB;
@@ -857,6 +862,51 @@ static double awq_md_cost(const MdTile& c, int64_t tiles, int splits, int groups
   return t;
 }
 
+static AwqPlan awq_plan_md(int M, int N, int K) {
+  AwqPlan p{};
+  p.groups = K / kAwqGroup;
+  const size_t up = 255;
+  double best = 0;
+  for (const MdTile& c : kMdTiles) {
+    if (c.mb > 1 && 32 * c.mb > M) continue;
+    const int tiles_m = (M + 32 * c.mb - 1) / (32 * c.mb);
+    const int tiles_n = (N + 64 * c.nw - 1) / (64 * c.nw);
+    const int64_t tiles = (int64_t)tiles_m * tiles_n;
+    for (int want = 1; want <= 16 && want <= p.groups; ++want) {
+      if (want > 1 && (tiles > awq_md::kMaxSplitTiles || c.nw != 4)) break;
+      const int gps = (p.groups + want - 1) / want;
+      const int splits = (p.groups + gps - 1) / gps;
+      if (splits != want) continue;
+      const double t = awq_md_cost(c, tiles, splits, gps, (int64_t)M * N);
+      if (p.md_mb == 0 || t < best) {
+        best = t;
+        p.md_mb = c.mb;
+        p.md_nw = c.nw;
+        p.tiles_m = tiles_m;
+        p.tiles_n = tiles_n;
+        p.tiles = tiles;
+        p.splits = splits;
+        p.groups_per_split = gps;
+      }
+    }
+  }
+  p.tiles_per_xcd = (int)((p.tiles + kNumXcd - 1) / kNumXcd);
+  // Counters, then the partials.  (More than 64 rows: sized as group sums of x
+  // and whole [M, N] planes.)
+  p.counter_bytes = kAwqCounterBytes;
+  if (M > 64)
+    p.counter_bytes = std::max(p.counter_bytes, ((size_t)p.groups * M * 16 + up) & ~up);
+  if (p.splits > 1) {
+    const size_t part = (size_t)p.splits * p.tiles * (32 * p.md_mb) * (64 * p.md_nw) *
+                        sizeof(float);
+    const size_t plane = (size_t)M * N * sizeof(float);
+    p.part_bytes = (part + plane - 1) / plane * plane;
+  } else if (M <= 64) {
+    p.counter_bytes = 0;
+  }
+  return p;
+}
+
 AwqPlan awq_plan(int M, int N, int K, bool small) {
   AwqPlan p{};
   p.groups = K / kAwqGroup;
@@ -869,50 +919,7 @@ AwqPlan awq_plan(int M, int N, int K, bool small) {
   // (gate_up at 32 rows 27 against 20, N = 12288 15.7 either way).
   const bool knobs = env_int("RAG_AWQ_SM_NB") > 0 || env_int("RAG_AWQ_SM_SPLITS") > 0;
   const bool wide = (M > 32 && (int64_t)N * K >= (int64_t)4608 * 4096) || (M > 16 && N > 16384);
-  if (M > 64 || (wide && !knobs && !small)) {
-    double best = 0;
-    for (const MdTile& c : kMdTiles) {
-      if (c.mb > 1 && 32 * c.mb > M) continue;
-      const int tiles_m = (M + 32 * c.mb - 1) / (32 * c.mb);
-      const int tiles_n = (N + 64 * c.nw - 1) / (64 * c.nw);
-      const int64_t tiles = (int64_t)tiles_m * tiles_n;
-      for (int want = 1; want <= 16 && want <= p.groups; ++want) {
-        if (want > 1 && (tiles > awq_md::kMaxSplitTiles || c.nw != 4)) break;
-        const int gps = (p.groups + want - 1) / want;
-        const int splits = (p.groups + gps - 1) / gps;
-        if (splits != want) continue;
-        const double t = awq_md_cost(c, tiles, splits, gps, (int64_t)M * N);
-        if (p.md_mb == 0 || t < best) {
-          best = t;
-          p.md_mb = c.mb;
-          p.md_nw = c.nw;
-          p.tiles_m = tiles_m;
-          p.tiles_n = tiles_n;
-          p.tiles = tiles;
-          p.splits = splits;
-          p.groups_per_split = gps;
-        }
-      }
-    }
-    p.tiles_per_xcd = (int)((p.tiles + kNumXcd - 1) / kNumXcd);
-    // Counters, then the partials.  The counters lie in the workspace's first
-    // kMinCounters bytes and the partials behind those and behind the counters
-    // that the small kernel may use for the same layer, so that batches of
-    // different sizes can follow each other in one workspace.  (More than 64
-    // rows: sized as group sums of x and whole [M, N] planes.)
-    p.counter_bytes = M > 64 ? ((size_t)p.groups * M * 16 + up) & ~up
-                             : std::max<size_t>(awq_md::kMinCounters,
-                                                ((size_t)N / 128 * sizeof(int) + up) & ~up);
-    if (p.splits > 1) {
-      const size_t part = (size_t)p.splits * p.tiles * (32 * p.md_mb) * (64 * p.md_nw) *
-                          sizeof(float);
-      const size_t plane = (size_t)M * N * sizeof(float);
-      p.part_bytes = (part + plane - 1) / plane * plane;
-    } else if (M <= 64) {
-      p.counter_bytes = 0;
-    }
-    return p;
-  }
+  if (M > 64 || (wide && !knobs && !small)) return awq_plan_md(M, N, K);
   // Small batches: a workgroup stages X of at most kXCap 16-row blocks, so
   // the groups are split at least groups * MB / kXCap ways, and no further:
   // the merge of a split (coherent partial stores, arrival count, reloads)
@@ -949,11 +956,13 @@ AwqPlan awq_plan(int M, int N, int K, bool small) {
   p.groups_per_split = (p.groups + splits - 1) / splits;
   p.splits = (p.groups + p.groups_per_split - 1) / p.groups_per_split;
   p.tiles = (int64_t)p.tiles_n * p.splits;
+  // (more column blocks than counters: the row-tiled kernel, which then has tiles
+  // enough without a split)
+  if (p.splits > 1 && p.tiles_n > kAwqCounters) return awq_plan_md(M, N, K);
   if (p.splits > 1) {
     // arrival counters first: zero-filled once by the caller, left zero by
     // every call
-    p.counter_bytes = std::max<size_t>(awq_md::kMinCounters,
-                                       ((size_t)p.tiles_n * sizeof(int) + up) & ~up);
+    p.counter_bytes = kAwqCounterBytes;
     p.part_bytes = ((size_t)p.splits * M * N * sizeof(float) + up) & ~up;
   }
   return p;

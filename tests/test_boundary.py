@@ -342,10 +342,11 @@ def test_awq_workspace_size():
     # (group, row), 256-byte rounded
     M, N, K = 4096, 4096, 4096
     assert ws(M, N, K) == (K // 128) * M * 16
-    # few 128-row output tiles: group sums plus a whole number of fp32
-    # [M, N] partial planes of a split over the groups
+    # few 128-row output tiles: group sums (at least the counter region, which
+    # is 64 KiB in every split call) plus a whole number of fp32 [M, N] partial
+    # planes of a split over the groups
     M, N, K = 200, 1024, 2048
-    pieces = -(-(K // 128) * M * 16 // 256) * 256
+    pieces = max(65536, -(-(K // 128) * M * 16 // 256) * 256)
     assert ws(M, N, K) > pieces and (ws(M, N, K) - pieces) % (M * N * 4) == 0
     # small batches (M <= 64): nothing when a workgroup's X fits its LDS
     # (qkv, o, gate_up of the 7B model at 16 rows); with the groups split over

@@ -78,3 +78,78 @@ def test_more_rows_than_counters_are_not_split():
     two = _decode(q, pool, lens, hkv, pool.block_tables, None, 2, None, rows)
     assert torch.equal(one.view(torch.int16), two.view(torch.int16))
     assert bool(torch.isfinite(two).all())
+
+
+def _linear(M, N, K, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    # every bit pattern is a valid packing of 4-bit codes
+    qw = torch.randint(-2 ** 31, 2 ** 31 - 1, (K // 128, N, 16), generator=g, device="cuda",
+                       dtype=torch.int32)
+    sc = ((torch.rand((K // 128, N), generator=g, device="cuda") + 0.5) / (6.5 * K ** 0.5))
+    z = torch.randint(0, 16, (K // 128, N), generator=g, device="cuda", dtype=torch.uint8)
+    return torch.randn((M, K), generator=g, device="cuda").bfloat16(), qw, sc.bfloat16(), z
+
+
+def _gemm(p, ws):
+    y = torch.full((p[0].shape[0], p[1].shape[1]), float("nan"), dtype=torch.bfloat16, device="cuda")
+    binding.rag_awq_gemm(*p, y, ws)
+    torch.cuda.synchronize()
+    return y
+
+
+def _codes(qw, cols):
+    """uint8 [K, len(cols)] of packed words (the layout of rag_awq_pack_weights)."""
+    w = qw[:, cols].cpu().numpy().view(np.uint32)               # [G, cols, 16]
+    out = np.zeros((w.shape[0], 128, len(cols)), dtype=np.uint8)
+    for i in range(16):
+        a, b, c = i >> 3, (i >> 2) & 1, i & 3
+        for j in range(8):
+            out[:, 8 * (4 * c + 2 * b + a) + j] = (w[:, :, i] >> (4 * (j // 2) + 16 * (j % 2))) & 15
+    return out.reshape(-1, len(cols))
+
+
+def _reference(p, cols):
+    x, qw, sc, z = p
+    g = np.arange(x.shape[1]) // 128
+    w = (_codes(qw, cols).astype(np.float64) - z[:, cols].cpu().numpy()[g]) * \
+        sc[:, cols].double().cpu().numpy()[g]
+    return x.double().cpu().numpy() @ w
+
+
+@pytest.mark.gpu
+def test_layers_of_any_width_share_a_workspace():
+    """Wide layers (hundreds of column blocks to count) and narrow split ones in
+    turn: the linear layers of a 70B model at 16 rows, and row-tiled splits."""
+    shapes = [(16, 10240, 8192), (16, 57344, 8192), (200, 1024, 2048), (16, 57344, 8192),
+              (16, 8192, 28672), (40, 4096, 14336), (16, 57344, 8192), (16, 10240, 8192)]
+    ws = torch.zeros(max(binding.rag_awq_workspace_size(*s) for s in shapes), dtype=torch.uint8,
+                     device="cuda")
+    for i, (M, N, K) in enumerate(shapes):
+        print(f"call {i}: M={M} N={N} K={K}", flush=True)
+        p = _linear(M, N, K, 60 + i)
+        own = torch.zeros(max(binding.rag_awq_workspace_size(M, N, K), 256), dtype=torch.uint8,
+                          device="cuda")
+        want, got = _gemm(p, own), _gemm(p, ws)
+        assert bool(torch.isfinite(got).all()), f"call {i}: columns left unwritten"
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)), f"call {i}"
+        cols = [0, 1, N // 2, N - 1]
+        # outputs of order 1: bf16 rounding, and fp32 sums of 128-term groups
+        assert np.abs(got[:, cols].double().cpu().numpy() - _reference(p, cols)).max() <= 2e-2
+
+
+def test_more_column_blocks_than_counters():
+    """A split small batch of more column blocks than counters is not split."""
+    assert binding.rag_awq_workspace_size(4, 128 * 16384, 4224) > 0
+    assert binding.rag_awq_workspace_size(4, 128 * 16385, 4224) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", [1, 5, 16])
+def test_more_column_blocks_than_counters_on_the_gpu(M):
+    N, K = 128 * 16385, 4224
+    p = _linear(M, N, K, 80 + M)
+    got = _gemm(p, torch.zeros(256, dtype=torch.uint8, device="cuda"))
+    assert bool(torch.isfinite(got).all())
+    cols = [0, 31, 32, 255, 256, N // 2 + 7, N - 1]
+    assert np.abs(got[:, cols].double().cpu().numpy() - _reference(p, cols)).max() <= 2e-2
