@@ -32,8 +32,9 @@ struct AwqPlan {
   size_t part_bytes;            // the partials of a split over the groups
 };
 
-// small: up to 64 rows, the small-batch kernel whatever the layer.
-AwqPlan awq_plan(int M, int N, int K, bool small = false);
+// The launch of a call that has avail bytes of workspace; with more than 16 rows
+// it fits whatever they are.
+AwqPlan awq_plan(int M, int N, int K, size_t avail = SIZE_MAX);
 hipError_t launch_awq_gemm(const AwqArgs& a, const AwqPlan& plan, hipStream_t stream);
 
 }  // namespace rag

@@ -3,6 +3,7 @@
 // weight packer.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "errors.h"
@@ -39,7 +40,10 @@ extern "C" {
 size_t rag_awq_workspace_size(int32_t M, int32_t N, int32_t K, int32_t group_size) {
   if (check_shape("awq workspace", M, N, K, group_size) != RAG_OK || M == 0) return 0;
   const rag::AwqPlan p = rag::awq_plan(M, N, K);
-  return p.counter_bytes + p.part_bytes;
+  const size_t need = p.counter_bytes + p.part_bytes;
+  if (M <= kTileM) return need;
+  // (never 0 above 64 rows: a program allocates what it is told, and passes it)
+  return std::max(need, ((size_t)(K / kGroup) * M * 16 + 255) & ~(size_t)255);
 }
 
 rag_status rag_awq_pack_weights(const uint8_t* q, int32_t K, int32_t N, int32_t group_size,
@@ -82,11 +86,9 @@ rag_status rag_awq_gemm(const void* x, const int32_t* qweight, const void* scale
       !aligned(zeros, 16))
     return fail(RAG_ERR_INVALID_ARG,
                 "awq gemm: x/qweight/scales/zeros/y must be 16-byte aligned");
-  rag::AwqPlan plan = rag::awq_plan(M, N, K);
+  const rag::AwqPlan plan = rag::awq_plan(M, N, K, workspace_bytes);
   const size_t need = plan.counter_bytes + plan.part_bytes;
-  // up to 64 rows the small-batch kernel may do with less
-  if (M <= kTileM && workspace && workspace_bytes < need) plan = rag::awq_plan(M, N, K, true);
-  if (!workspace || workspace_bytes < plan.counter_bytes + plan.part_bytes)
+  if (!workspace || workspace_bytes < need)
     return fail(RAG_ERR_WORKSPACE, "awq gemm: workspace of %zu bytes needed, %zu given", need,
                 workspace ? workspace_bytes : (size_t)0);
   if (!aligned(workspace, 256))

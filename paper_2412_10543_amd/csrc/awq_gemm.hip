@@ -26,6 +26,7 @@
 // are words 8h .. 8h+7 (step t at 8h + 4(t&1) + t/2); a 16x16x32 lane
 // (column, quarter qq) needs the octets 4t + qq of k-steps t = 0..3, words
 // 8(qq&1) + 4(qq>>1) .. +3.
+#include <cstdint>
 #include <cstdlib>
 
 #include "common.h"
@@ -862,21 +863,30 @@ static double awq_md_cost(const MdTile& c, int64_t tiles, int splits, int groups
   return t;
 }
 
-static AwqPlan awq_plan_md(int M, int N, int K) {
+// The best tile and split of awq_gemm_md_kernel in avail bytes of workspace (an
+// unsplit launch needs none).  Counters, then the partials, sized as whole [M, N]
+// planes; more than 64 rows: behind group sums of x.
+static AwqPlan awq_plan_md(int M, int N, int K, size_t avail) {
   AwqPlan p{};
   p.groups = K / kAwqGroup;
   const size_t up = 255;
+  size_t front = kAwqCounterBytes;
+  if (M > 64) front = std::max(front, ((size_t)p.groups * M * 16 + up) & ~up);
   double best = 0;
   for (const MdTile& c : kMdTiles) {
     if (c.mb > 1 && 32 * c.mb > M) continue;
     const int tiles_m = (M + 32 * c.mb - 1) / (32 * c.mb);
     const int tiles_n = (N + 64 * c.nw - 1) / (64 * c.nw);
     const int64_t tiles = (int64_t)tiles_m * tiles_n;
+    const size_t plane = (size_t)M * N * sizeof(float);
+    const size_t out = (size_t)tiles * (32 * c.mb) * (64 * c.nw) * sizeof(float);
     for (int want = 1; want <= 16 && want <= p.groups; ++want) {
       if (want > 1 && (tiles > awq_md::kMaxSplitTiles || c.nw != 4)) break;
       const int gps = (p.groups + want - 1) / want;
       const int splits = (p.groups + gps - 1) / gps;
       if (splits != want) continue;
+      const size_t part = splits > 1 ? (splits * out + plane - 1) / plane * plane : 0;
+      if (splits > 1 && (avail < front || avail - front < part)) continue;
       const double t = awq_md_cost(c, tiles, splits, gps, (int64_t)M * N);
       if (p.md_mb == 0 || t < best) {
         best = t;
@@ -887,39 +897,19 @@ static AwqPlan awq_plan_md(int M, int N, int K) {
         p.tiles = tiles;
         p.splits = splits;
         p.groups_per_split = gps;
+        p.counter_bytes = splits > 1 ? front : 0;
+        p.part_bytes = part;
       }
     }
   }
   p.tiles_per_xcd = (int)((p.tiles + kNumXcd - 1) / kNumXcd);
-  // Counters, then the partials.  (More than 64 rows: sized as group sums of x
-  // and whole [M, N] planes.)
-  p.counter_bytes = kAwqCounterBytes;
-  if (M > 64)
-    p.counter_bytes = std::max(p.counter_bytes, ((size_t)p.groups * M * 16 + up) & ~up);
-  if (p.splits > 1) {
-    const size_t part = (size_t)p.splits * p.tiles * (32 * p.md_mb) * (64 * p.md_nw) *
-                        sizeof(float);
-    const size_t plane = (size_t)M * N * sizeof(float);
-    p.part_bytes = (part + plane - 1) / plane * plane;
-  } else if (M <= 64) {
-    p.counter_bytes = 0;
-  }
   return p;
 }
 
-AwqPlan awq_plan(int M, int N, int K, bool small) {
+static AwqPlan awq_plan_sm(int M, int N, int K) {
   AwqPlan p{};
   p.groups = K / kAwqGroup;
   const size_t up = 255;
-  p.splits = 1;
-  p.groups_per_split = p.groups;
-  // awq_gemm_sm_kernel for up to 64 rows except where its tiles are the slower
-  // ones: 33-64 rows of a layer above the 7B o_proj's size (7B gate_up at 64
-  // rows 49 us against 29, o_proj 14.0 against 15.1), 17-32 rows of a wide one
-  // (gate_up at 32 rows 27 against 20, N = 12288 15.7 either way).
-  const bool knobs = env_int("RAG_AWQ_SM_NB") > 0 || env_int("RAG_AWQ_SM_SPLITS") > 0;
-  const bool wide = (M > 32 && (int64_t)N * K >= (int64_t)4608 * 4096) || (M > 16 && N > 16384);
-  if (M > 64 || (wide && !knobs && !small)) return awq_plan_md(M, N, K);
   // Small batches: a workgroup stages X of at most kXCap 16-row blocks, so
   // the groups are split at least groups * MB / kXCap ways, and no further:
   // the merge of a split (coherent partial stores, arrival count, reloads)
@@ -956,9 +946,6 @@ AwqPlan awq_plan(int M, int N, int K, bool small) {
   p.groups_per_split = (p.groups + splits - 1) / splits;
   p.splits = (p.groups + p.groups_per_split - 1) / p.groups_per_split;
   p.tiles = (int64_t)p.tiles_n * p.splits;
-  // (more column blocks than counters: the row-tiled kernel, which then has tiles
-  // enough without a split)
-  if (p.splits > 1 && p.tiles_n > kAwqCounters) return awq_plan_md(M, N, K);
   if (p.splits > 1) {
     // arrival counters first: zero-filled once by the caller, left zero by
     // every call
@@ -966,6 +953,30 @@ AwqPlan awq_plan(int M, int N, int K, bool small) {
     p.part_bytes = ((size_t)p.splits * M * N * sizeof(float) + up) & ~up;
   }
   return p;
+}
+
+AwqPlan awq_plan(int M, int N, int K, size_t avail) {
+  if (M > 64) return awq_plan_md(M, N, K, avail);
+  // awq_gemm_sm_kernel for up to 64 rows except where its tiles are the slower
+  // ones: 33-64 rows of a layer above the 7B o_proj's size (7B gate_up at 64
+  // rows 49 us against 29, o_proj 14.0 against 15.1), 17-32 rows of a wide one
+  // (gate_up at 32 rows 27 against 20, N = 12288 15.7 either way).
+  const bool knobs = env_int("RAG_AWQ_SM_NB") > 0 || env_int("RAG_AWQ_SM_SPLITS") > 0;
+  const bool wide = (M > 32 && (int64_t)N * K >= (int64_t)4608 * 4096) || (M > 16 && N > 16384);
+  const AwqPlan sm = awq_plan_sm(M, N, K);
+  // (more column blocks than counters: the row-tiled kernel has tiles enough
+  // without a split)
+  if (sm.splits > 1 && sm.tiles_n > kAwqCounters) return awq_plan_md(M, N, K, avail);
+  auto fits = [avail](const AwqPlan& p) { return p.counter_bytes + p.part_bytes <= avail; };
+  if (wide && !knobs) {
+    const AwqPlan md = awq_plan_md(M, N, K, SIZE_MAX);
+    if (fits(md)) return md;
+  }
+  // Up to 16 rows the small kernel's split needs its workspace, as it always has
+  // (a call that brings less is refused); more rows fall back to the row-tiled
+  // kernel in what there is.
+  if (fits(sm) || M <= 16 || knobs) return sm;
+  return awq_plan_md(M, N, K, avail);
 }
 
 hipError_t launch_awq_gemm(const AwqArgs& a, const AwqPlan& p, hipStream_t stream) {

@@ -153,3 +153,24 @@ def test_more_column_blocks_than_counters_on_the_gpu(M):
     assert bool(torch.isfinite(got).all())
     cols = [0, 31, 32, 255, 256, N // 2 + 7, N - 1]
     assert np.abs(got[:, cols].double().cpu().numpy() - _reference(p, cols)).max() <= 2e-2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,K,batch,rows", [
+    (4096, 14336, 64, [1, 9, 16, 17, 31, 32, 33, 37, 40, 48, 58, 63, 64]),   # 7B down
+    (28672, 4096, 64, [7, 16, 17, 32, 33, 47, 58, 64]),                      # 7B gate_up
+    (4096, 4096, 1024, [16, 40, 65, 96, 128, 200, 320, 511, 700, 1024]),     # 7B o
+    (1024, 2048, 0, [17, 40, 64, 65, 200, 320])])                            # nothing to spare
+def test_smaller_batches_fit_a_larger_ones_workspace(N, K, batch, rows):
+    """A workspace sized for a layer's largest batch takes every smaller one
+    (the split is then the best that fits it)."""
+    size = binding.rag_awq_workspace_size(batch, N, K) if batch else 256
+    ws = torch.zeros(max(size, 256), dtype=torch.uint8, device="cuda")
+    cols = [0, 33, N // 2, N - 1]
+    full = _linear(max(rows), N, K, 90 + N % 7)
+    want = _reference(full, cols)
+    for M in rows:
+        print(f"M={M}", flush=True)
+        got = _gemm((full[0][:M],) + full[1:], ws)
+        assert bool(torch.isfinite(got).all())
+        assert np.abs(got[:, cols].double().cpu().numpy() - want[:M]).max() <= 2e-2
