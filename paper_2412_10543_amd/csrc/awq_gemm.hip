@@ -962,8 +962,16 @@ AwqPlan awq_plan(int M, int N, int K, size_t avail) {
   // rows 49 us against 29, o_proj 14.0 against 15.1), 17-32 rows of a wide one
   // (gate_up at 32 rows 27 against 20, N = 12288 15.7 either way).
   const bool knobs = env_int("RAG_AWQ_SM_NB") > 0 || env_int("RAG_AWQ_SM_SPLITS") > 0;
-  const bool wide = (M > 32 && (int64_t)N * K >= (int64_t)4608 * 4096) || (M > 16 && N > 16384);
+  // Where the small kernel needs no split and a workgroup a CU it stays the faster
+  // one, whatever the width (17 rows: N = 32768, K = 1024 8.1 us against 10.8, 28672
+  // x 2048 11.0 against 15.4; the shortest K the other way, 28672 x 128 4.3 against
+  // 3.7).  Over 480 shapes of 17-64 rows the choice is at most 4% slower than the
+  // small kernel, which is up to twice as slow as the choice.
   const AwqPlan sm = awq_plan_sm(M, N, K);
+  const bool one_wave =
+      sm.splits == 1 && sm.tiles_n <= kAwqCus && K >= (M > 32 ? 1024 : 512);
+  const bool wide = !one_wave && ((M > 32 && (int64_t)N * K >= (int64_t)4608 * 4096) ||
+                                  (M > 16 && N > 16384));
   // (more column blocks than counters: the row-tiled kernel has tiles enough
   // without a split)
   if (sm.splits > 1 && sm.tiles_n > kAwqCounters) return awq_plan_md(M, N, K, avail);

@@ -10,6 +10,7 @@ import torch
 from paper_2412_10543_amd import binding
 from paper_2412_10543_amd.workloads import awq_problem
 
+import gpu_support as G_
 from test_gpu_awq import _check, _device, _run
 
 pytestmark = pytest.mark.gpu
@@ -78,9 +79,25 @@ def test_one_workspace_for_every_shape():
 
 def test_small_workspace_takes_the_small_batch_kernel():
     """32 rows of a layer that the row-tiled kernel would split: a call that
-    brings only what the small-batch kernel needs (nothing) still runs."""
-    M, N, K = 32, 16512, 2048
-    assert binding.rag_awq_workspace_size(M, N, K) > 256
+    brings only what the small-batch kernel needs takes that one (the bits of
+    the knob that asks for it).  (K one group longer than the small kernel takes
+    without a split: layers up to there are its own.)"""
+    M, N, K = 32, 16512, 2176
     p = awq_problem(M, N, K, seed=3, device="cuda")
-    ws = torch.zeros(256, dtype=torch.uint8, device="cuda")
-    _check(p, _run(p, *_device(p), ws=ws), cols=list(range(0, N, 31)))
+    dev = _device(p)
+    with G_.env("RAG_AWQ_SM_SPLITS", 1):
+        size = binding.rag_awq_workspace_size(M, N, K)
+        small = _run(p, *dev)
+    assert binding.rag_awq_workspace_size(M, N, K) > size
+    y = _run(p, *dev, ws=torch.zeros(size, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(y.view(torch.int16), small.view(torch.int16))
+    _check(p, y, cols=list(range(0, N, 31)))
+
+
+@pytest.mark.parametrize("M,N,K", [(17, 32768, 512), (32, 16512, 2048), (33, 32768, 1024),
+                                   (64, 20480, 1024), (17, 32896, 512), (40, 18432, 1152)])
+def test_wide_layers_at_the_small_kernels_edge(M, N, K):
+    """17 to 64 rows of wide layers on both sides of the small kernel's limits:
+    256 workgroups, no split."""
+    p = awq_problem(M, N, K, seed=M + N + K, device="cuda")
+    _check(p, _run(p, *_device(p)), cols=list(range(0, N, 61)) + [N - 1])
