@@ -466,13 +466,13 @@ rag_status rag_device_free_memory(size_t *free_bytes, size_t *total_bytes);
 rag_status rag_awq_pack_weights(const uint8_t *q, int32_t K, int32_t N,
                                 int32_t group_size, int32_t *packed);
 
-/* Bytes of workspace rag_awq_gemm needs (0 for M == 0, invalid shapes, or
- * a small batch that needs none).  Library-internal layout: 16,384 int32
- * arrival counters (as many for every call), then fp32 partial outputs where the
- * weight groups are split over workgroups (few output tiles or column blocks, or
- * a long K in a small batch).  M > 64: the larger of those counters and K / 128 *
- * M * 16 bytes (rounded up to 256), then whole planes of M * N * 4 bytes.
- * Partials are added in a fixed order, so results do not depend on
+/* Bytes of workspace rag_awq_gemm uses (0 for M == 0, invalid shapes, or a
+ * small batch that uses none).  Library-internal layout: 16,384 int32 arrival
+ * counters (as many for every call), then fp32 partial outputs where the weight
+ * groups are split over workgroups (few output tiles or column blocks, or a long
+ * K in a small batch); M > 64: never less than the counters.  With less, and more
+ * than 16 rows, rag_awq_gemm takes the best split that fits (none needs nothing
+ * but a pointer).  Partials are added in a fixed order, so results do not depend on
  * timing.  For M <= 64 the environment variables RAG_AWQ_SM_NB (16-column
  * blocks per workgroup: 1, 2, 4 or 8) and RAG_AWQ_SM_SPLITS (at least this many
  * splits) take the small-batch kernel and override its choice, read at each
@@ -487,10 +487,10 @@ size_t rag_awq_workspace_size(int32_t M, int32_t N, int32_t K,
  *   scales   device bf16 [K / 128, N]
  *   zeros    device uint8 [K / 128, N], each 0..15
  *   y        device bf16 [M, N]; output, written in full
- *   workspace  device, >= rag_awq_workspace_size(M, N, K, group_size) bytes,
- *            256-byte aligned, zero-filled once before its first use: it
- *            starts with the arrival counters of a split over the weight
- *            groups, which every call leaves at zero again.  Calls of any
+ *   workspace  device, rag_awq_workspace_size(M, N, K, group_size) bytes (M <= 16:
+ *            no fewer; not NULL), 256-byte aligned, zero-filled once before its
+ *            first use: it starts with the arrival counters of a split over the
+ *            weight groups, which every call leaves at zero again.  Calls of any
  *            layers and batches may follow each other in it; overlapping calls
  *            must not share it.
  * Returns RAG_OK (M == 0 is a no-op; x and y may then be NULL),

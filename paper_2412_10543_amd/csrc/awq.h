@@ -9,6 +9,13 @@
 
 namespace rag {
 
+// Arrival counters at a workspace's start, one per column block or output tile
+// of a split launch, at most: the same bytes for every call, as the partials
+// behind them keep what the last call wrote and calls of any layer and batch
+// may follow each other in one workspace.
+constexpr int kAwqCounters = 16384;
+constexpr size_t kAwqCounterBytes = kAwqCounters * sizeof(int);
+
 struct AwqArgs {
   const void* x;                // bf16 [M, K]
   const int32_t* qweight;       // packed codes [K/128][N][16]

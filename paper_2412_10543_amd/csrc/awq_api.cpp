@@ -43,7 +43,7 @@ size_t rag_awq_workspace_size(int32_t M, int32_t N, int32_t K, int32_t group_siz
   const size_t need = p.counter_bytes + p.part_bytes;
   if (M <= kTileM) return need;
   // (never 0 above 64 rows: a program allocates what it is told, and passes it)
-  return std::max(need, ((size_t)(K / kGroup) * M * 16 + 255) & ~(size_t)255);
+  return std::max(need, rag::kAwqCounterBytes);
 }
 
 rag_status rag_awq_pack_weights(const uint8_t* q, int32_t K, int32_t N, int32_t group_size,

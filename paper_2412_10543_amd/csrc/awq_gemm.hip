@@ -36,12 +36,6 @@ namespace rag {
 
 constexpr int kAwqGroup = 128;
 constexpr int kAwqCus = 256;     // MI355X compute units
-// Arrival counters at a workspace's start, one per column block or output tile
-// of a split launch, at most: the same bytes for every call, as the partials
-// behind them keep what the last call wrote and calls of any layer and batch
-// may follow each other in one workspace.
-constexpr int kAwqCounters = 16384;
-constexpr size_t kAwqCounterBytes = kAwqCounters * sizeof(int);
 
 // A value the compiler must keep in a VGPR (no constant folding).
 __device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
@@ -863,30 +857,26 @@ static double awq_md_cost(const MdTile& c, int64_t tiles, int splits, int groups
   return t;
 }
 
-// The best tile and split of awq_gemm_md_kernel in avail bytes of workspace (an
-// unsplit launch needs none).  Counters, then the partials, sized as whole [M, N]
-// planes; more than 64 rows: behind group sums of x.
+// The best tile and split of awq_gemm_md_kernel in avail bytes of workspace:
+// counters, then the partials of a split, in whole tiles (none unsplit).
 static AwqPlan awq_plan_md(int M, int N, int K, size_t avail) {
   AwqPlan p{};
   p.groups = K / kAwqGroup;
-  const size_t up = 255;
-  size_t front = kAwqCounterBytes;
-  if (M > 64) front = std::max(front, ((size_t)p.groups * M * 16 + up) & ~up);
   double best = 0;
   for (const MdTile& c : kMdTiles) {
     if (c.mb > 1 && 32 * c.mb > M) continue;
     const int tiles_m = (M + 32 * c.mb - 1) / (32 * c.mb);
     const int tiles_n = (N + 64 * c.nw - 1) / (64 * c.nw);
     const int64_t tiles = (int64_t)tiles_m * tiles_n;
-    const size_t plane = (size_t)M * N * sizeof(float);
     const size_t out = (size_t)tiles * (32 * c.mb) * (64 * c.nw) * sizeof(float);
     for (int want = 1; want <= 16 && want <= p.groups; ++want) {
       if (want > 1 && (tiles > awq_md::kMaxSplitTiles || c.nw != 4)) break;
       const int gps = (p.groups + want - 1) / want;
       const int splits = (p.groups + gps - 1) / gps;
       if (splits != want) continue;
-      const size_t part = splits > 1 ? (splits * out + plane - 1) / plane * plane : 0;
-      if (splits > 1 && (avail < front || avail - front < part)) continue;
+      const size_t counters = splits > 1 ? kAwqCounterBytes : 0;
+      const size_t part = splits > 1 ? splits * out : 0;
+      if (counters + part > avail) continue;
       const double t = awq_md_cost(c, tiles, splits, gps, (int64_t)M * N);
       if (p.md_mb == 0 || t < best) {
         best = t;
@@ -897,7 +887,7 @@ static AwqPlan awq_plan_md(int M, int N, int K, size_t avail) {
         p.tiles = tiles;
         p.splits = splits;
         p.groups_per_split = gps;
-        p.counter_bytes = splits > 1 ? front : 0;
+        p.counter_bytes = counters;
         p.part_bytes = part;
       }
     }

@@ -338,16 +338,14 @@ def test_awq_workspace_size():
     ws = binding.rag_awq_workspace_size
     assert ws(0, 256, 512) == 0
     assert ws(64, 256, 500) == 0 and ws(64, 256, 512, 64) == 0
-    # enough tiles to fill the GPU: only the group-sum pieces, 16 bytes per
-    # (group, row), 256-byte rounded
-    M, N, K = 4096, 4096, 4096
-    assert ws(M, N, K) == (K // 128) * M * 16
-    # few 128-row output tiles: group sums (at least the counter region, which
-    # is 64 KiB in every split call) plus a whole number of fp32 [M, N] partial
-    # planes of a split over the groups
+    # enough tiles to fill the GPU: no split, so only the counter region that
+    # every split call starts with (the kernel forms the group sums itself)
+    assert ws(4096, 4096, 4096) == 65536 and ws(8192, 4096, 14336) == 65536
+    # few output tiles: counters plus fp32 partials of a split over the groups, in
+    # whole tiles of at least 32 rows x 256 columns that cover [M, N]
     M, N, K = 200, 1024, 2048
-    pieces = max(65536, -(-(K // 128) * M * 16 // 256) * 256)
-    assert ws(M, N, K) > pieces and (ws(M, N, K) - pieces) % (M * N * 4) == 0
+    part = ws(M, N, K) - 65536
+    assert part % (32 * 256 * 4) == 0 and part >= 2 * M * N * 4
     # small batches (M <= 64): nothing when a workgroup's X fits its LDS
     # (qkv, o, gate_up of the 7B model at 16 rows); with the groups split over
     # workgroups, counters for at least N / 128 column blocks
