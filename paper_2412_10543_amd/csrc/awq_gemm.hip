@@ -67,54 +67,48 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | ((n >> 4) << 14));
 }
 
-// Per-column constants of one group from its bf16 scale bits: c = sign * m,
-// the conversion mask and magic (exponent field 134 + e), and the bf16 bits of
-// -(128 + z) 2^e.  Scales of 2^121 and above keep the excess power of two in
-// c; a zero scale gives mask = magic = nz = 0 and c = 0 (the caller keeps its
-// reference); inf or NaN gives c = NaN.
+// Per-column constants of one group from its bf16 scale bits: c = sign * m, the
+// conversion mask and magic (exponent field 134 + e), and the bf16 bits of
+// -(128 + z) 2^e.  Scales of 2^41 and above keep the excess power of two in c:
+// (128 + q) 2^e x is summed before the zero point cancels most of it, and no
+// scale may take that sum out of range that leaves the result in it.
 struct ColScale {
   float c;
   uint32_t mask, magic, nz;
 };
-__device__ __forceinline__ ColScale col_scale(uint32_t sb, uint32_t z) {
-  const uint32_t E = (sb >> 7) & 0xFFu, mt = sb & 0x7Fu;
-  int e;
-  uint32_t mbits;
-  if (E == 0) {                                   // bf16 subnormal: mt * 2^-133
-    const int k = 31 - __builtin_clz(mt | 1u);
-    mbits = (mt << (7 - k)) & 0x7Fu;
-    e = k - 133;
-  } else {
-    mbits = mt;
-    e = (int)E - 127;
-  }
-  const int eb = min(e, 120);
-  float c = bf16_to_f32((sb & 0x8000u) | 0x3F80u | mbits);
-  if (e > eb) c = ldexpf(c, e - eb);
-  if (E == 0xFFu) c = __builtin_nanf("");
-  const bool zero = (sb & 0x7FFFu) == 0;
-  const uint32_t ex = (uint32_t)(134 + eb) << 7;
-  ColScale r;
-  r.c = zero ? 0.f : c;
-  r.mask = zero ? 0u : 0x000F000Fu;
-  r.magic = zero ? 0u : ex | (ex << 16);
-  r.nz = zero ? 0u : 0x8000u | ex | z;
-  return r;
-}
-
-// The same for scales that are all normal and below 2^121 (the caller's check,
-// plain_scale): 12 instructions instead of 30.
+constexpr uint32_t kMaxOperandExp = 127 + 40;
+// Normal scales (plain_scale): 13 instructions.
 __device__ __forceinline__ bool plain_scale(uint32_t sb) {
   const uint32_t E = sb & 0x7F80u;
-  return E - 0x80u < (248u << 7) - 0x80u;
+  return E - 0x80u < 0x7F80u - 0x80u;
 }
 __device__ __forceinline__ ColScale col_scale_plain(uint32_t sb, uint32_t z) {
-  const uint32_t ex = (sb & 0x7F80u) + (7u << 7);       // exponent field 134 + e
+  const uint32_t field = min(sb & 0x7F80u, kMaxOperandExp << 7);
+  const uint32_t ex = field + (7u << 7);                // exponent field 134 + e
   ColScale r;
-  r.c = bf16_to_f32((sb & 0x807Fu) | 0x3F80u);
+  r.c = bf16_to_f32(sb - field + 0x3F80u);
   r.mask = 0x000F000Fu;
   r.magic = ex | (ex << 16);
   r.nz = 0x8000u | ex | z;
+  return r;
+}
+// The others.  A zero scale gives mask = magic = nz = 0 and c = 0 (the caller
+// keeps its reference).  Infinity gives c = infinity: the caller's u, y / c, drops
+// what it held (0 where that was finite) and takes the group's own sum, which
+// times c is infinity of its sign, or NaN where it is 0, as y + inf * sum is.  (A
+// second infinite scale in a column of one workgroup's groups gives NaN.)
+__device__ __forceinline__ ColScale col_scale(uint32_t sb, uint32_t z) {
+  if (plain_scale(sb)) return col_scale_plain(sb, z);
+  const uint32_t mt = sb & 0x7Fu;
+  const int k = 31 - __builtin_clz(mt | 1u);            // subnormal: mt * 2^-133
+  const bool subnormal = (sb & 0x7F80u) == 0, zero = subnormal && mt == 0;
+  const uint32_t ex = (uint32_t)(134 + (subnormal ? k - 133 : 0)) << 7;
+  const float m = bf16_to_f32((sb & 0x8000u) | 0x3F80u | ((mt << (7 - k)) & 0x7Fu));
+  ColScale r;
+  r.c = zero ? 0.f : subnormal ? m : bf16_to_f32(sb);   // (infinity or NaN as it is)
+  r.mask = zero ? 0u : 0x000F000Fu;
+  r.magic = zero ? 0u : ex | (ex << 16);
+  r.nz = zero ? 0u : 0x8000u | ex | z;
   return r;
 }
 

@@ -4,6 +4,8 @@ small-batch kernel, column counts that leave half a tile, one group, and splits
 of the groups; calls of different shapes sharing one workspace.  Tolerance as in
 test_gpu_awq.py (its arithmetic is the same: exact products, fp32 sums, one
 rescale per group)."""
+import dataclasses
+
 import pytest
 import torch
 
@@ -101,3 +103,46 @@ def test_wide_layers_at_the_small_kernels_edge(M, N, K):
     256 workgroups, no split."""
     p = awq_problem(M, N, K, seed=M + N + K, device="cuda")
     _check(p, _run(p, *_device(p)), cols=list(range(0, N, 61)) + [N - 1])
+
+
+def _small_kernel(p, dev):
+    """The same call 64 rows at a time through the small-batch kernel (one fp32
+    FMA per group and output: y + s (P - (128 + z) S))."""
+    x, out = p.x, []
+    with G_.env("RAG_AWQ_SM_SPLITS", 1):
+        for r in range(0, x.shape[0], 64):
+            out.append(_run(dataclasses.replace(p, x=x[r:r + 64].contiguous()), *dev))
+    return torch.cat(out)
+
+
+@pytest.mark.parametrize("M,N,K", [(20, 16512, 2176), (48, 4608, 4096), (130, 512, 1024),
+                                   (320, 640, 896), (1200, 256, 256)])
+def test_scales_and_rows_that_are_not_ordinary(M, N, K):
+    """Infinite, NaN, huge and subnormal scales (one such group a column), and
+    rows with an infinity, a NaN or nothing but zeros: finite, infinite and NaN
+    outputs as from the small-batch kernel."""
+    p = awq_problem(M, N, K, seed=M + K, device="cuda")
+    kinds = [float("inf"), -float("inf"), float("nan"), 2.0 ** 118, 2.0 ** 127, -2.0 ** 100,
+             2.0 ** -130, None, 2.0 ** 41, -2.0 ** 40, 1.5 * 2.0 ** 121]
+    s = p.scales.float()
+    for col in range(N):
+        v = kinds[col % len(kinds)]
+        if v is not None:
+            s[(col // len(kinds)) % s.shape[0], col] = v
+    p.scales = s.to(torch.bfloat16)
+    p.x[1, 5], p.x[M // 2, K - 1], p.x[3] = float("inf"), float("nan"), 0.0
+    dev = _device(p)
+    y, ref = _run(p, *dev).double(), _small_kernel(p, dev).double()
+    assert torch.equal(y.isnan(), ref.isnan())
+    assert torch.equal(y.isinf(), ref.isinf()) and torch.equal(y.sign()[y.isinf()],
+                                                               ref.sign()[y.isinf()])
+    ok = y.isfinite()
+    assert bool(ok.any()) and not bool(ok.all())
+    # both within test_gpu_awq's bound of the exact sum: half an ulp of bf16 each,
+    # and the fp32 sums' part of the magnitudes A entering them
+    g = torch.arange(K, device="cuda") // 128
+    mag = (torch.from_numpy(p.codes).cuda().double() + dev[2][g].double() + 256) * \
+        dev[1][g].double().abs()
+    A = p.x.double().abs().nan_to_num(0.0, posinf=0.0) @ mag.nan_to_num(0.0, posinf=0.0)
+    bound = 2.0 ** -7 * ref.abs() + 2 * (2.0 ** -17 + (K // 128) * 2.0 ** -22) * A
+    assert bool(((y - ref).abs() <= bound)[ok].all())
