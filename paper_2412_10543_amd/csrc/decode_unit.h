@@ -49,7 +49,7 @@ struct DecodeOut {
 // the same launch, see decode_unit).
 template <int D, int NP, bool kAppend = false>
 __device__ __forceinline__ void decode_wave(
-    int tid, const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
+    int tid, bool mask, const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
     const bf16_t* __restrict__ vc, size_t block_stride, const int32_t* __restrict__ table,
     int kv_len, int group, int p_first, int p_end, int p_stride, float scale,
     bf16_t* __restrict__ vt,
@@ -63,17 +63,18 @@ __device__ __forceinline__ void decode_wave(
   const int l16 = lane & 15, gq = lane >> 4;
 
   // Q^T fragments: lane holds head l16, d = 32*ks + 8*gq .. +8.  Lanes past the
-  // group repeat its last head (no masked loads; their results are not used, and
-  // their scores move no maximum that the last head's do not), or hold zeros in
-  // the appending kernels, which are faster so (221 rows of 37-590 keys and 16
-  // kv heads: 73.5 us against 74.6; the mixed launch the other way round, 1736
-  // against 1719).
+  // group hold zeros (mask), or, in the mixed launch's eight-wave units, repeat its
+  // last head (no masked loads; their results are not used, and their scores move
+  // no maximum that the last head's do not): 1719 us there against 1736, but
+  // four-wave units are faster masked (140 batches of 4-320 rows 0.4% on average,
+  // 20 of 100-200 keys 2%; appending, 221 of 37-590 and 16 kv heads 73.5 against
+  // 74.6).
   bf16x8 qf[kKs];
-  const bf16_t* ql = q + (kAppend ? l16 : min(l16, group - 1)) * D + gq * 8;
+  const bf16_t* ql = q + (mask ? l16 : min(l16, group - 1)) * D + gq * 8;
 #pragma unroll
   for (int ks = 0; ks < kKs; ++ks) {
     u32x4 z = {0, 0, 0, 0};
-    qf[ks] = as_bf16x8(!kAppend || l16 < group ? load16(ql + ks * 32) : z);
+    qf[ks] = as_bf16x8(!mask || l16 < group ? load16(ql + ks * 32) : z);
   }
 #pragma unroll
   for (int dt = 0; dt < kDt; ++dt) oacc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -312,7 +313,7 @@ __device__ __forceinline__ void decode_unit(
   }
   f32x4 oacc[kDt];
   float m_used, l;
-  decode_wave<D, NP, kAppend>(tid, q, kc, vc, block_stride, table, kv_len, group,
+  decode_wave<D, NP, kAppend>(tid, W <= 4, q, kc, vc, block_stride, table, kv_len, group,
                               p_begin + wave * NP, p_end, W * NP, scale,
                               lds + wave * L::kElemsWave, oacc, m_used, l, k_new, v_new);
 

@@ -427,12 +427,6 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
     uncut = long_rows == 0;
   }
   int total = 0, longest = 0;
-  auto longest_row = [&] {
-    int m = pg[0];
-#pragma unroll
-    for (int c = 1; c < kChunks; ++c) m = max(m, pg[c]);
-    return (int)__builtin_amdgcn_readlane(wave_scan_max(m), 63);
-  };
   if (!uncut) {
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) {
@@ -441,7 +435,9 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
       total += __builtin_amdgcn_readlane(incl, 63);
     }
     if constexpr (kFull) {
-      longest = longest_row();
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) longest = max(longest, pg[c]);
+      longest = __builtin_amdgcn_readlane(wave_scan_max(longest), 63);
       uncut = !bal_skewed<D>(S, a.bal_units, total, longest, group);
     }
   }
@@ -458,7 +454,14 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
   // workspace has slots for (a crossing row also starts and ends inside one).
   float q_min = (float)kDecMinPages;
   if (a.bal_units > a.slots) {
-    if constexpr (!kFull) longest = longest_row();
+    if constexpr (!kFull) {                  // (not the scan: 0.8% on 20 rows of 600 keys)
+      longest = pg[0];
+#pragma unroll
+      for (int c = 1; c < kChunks; ++c) longest = max(longest, pg[c]);
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) longest = max(longest, __shfl_xor(longest, m, kWave));
+      longest = __builtin_amdgcn_readfirstlane(longest);
+    }
     q_min = fmaxf(q_min, (float)longest * __builtin_amdgcn_rcpf((float)(a.slots - 2)) + 2.f);
   }
   // Whole pieces: quotas from the larger of q_min and the mean per unit on, up
