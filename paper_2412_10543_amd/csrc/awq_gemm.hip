@@ -114,11 +114,12 @@ __device__ __forceinline__ ColScale col_scale(uint32_t sb, uint32_t z) {
 
 // ---------------------------------------------------------------------------
 // Larger batches: workgroups of NW waves own 32 MB x 64 NW tiles of Y; wave w
-// computes all rows and the columns 64 w .. +64 as MB x 2 MFMA blocks of 32 x 32.  The X tile of a group is shared through LDS (direct global -> LDS
-// copies one group ahead, two stages; row r's 16-byte chunk c at position
-// c ^ (r & 15), so that the A reads of 16 rows hit 16 distinct bank groups);
-// the code words, scales and zero points belong to one wave only and go from
-// memory straight into its registers, one group ahead.
+// computes all rows and the columns 64 w .. +64 as MB x 2 MFMA blocks of 32 x 32.
+// The X tile of a group is shared through LDS (direct global -> LDS copies one
+// group ahead, two stages; row r's 16-byte chunk c at position c ^ (r & 15), so
+// that the A reads of 16 rows hit 16 distinct bank groups); the code words, scales
+// and zero points belong to one wave only and go from memory straight into its
+// registers, one group ahead.
 //
 // Group sums.  Each wave sums its share of the rows of the X tile (one lane per
 // row and half of a k-step, v_dot2 with ones) and stores the sums as three
@@ -450,8 +451,8 @@ awq_gemm_md_kernel(const bf16_t* __restrict__ x, const uint32_t* __restrict__ qw
 
   // ---- groups split over workgroups: fp32 partials (device-coherent stores,
   // another XCD may add them), then the last workgroup of the tile to arrive
-  // adds them in split order, its own from registers, and leaves the tile's
-  // counter at zero ----
+  // reads all of them back (its own too), adds them in split order and leaves the
+  // tile's counter at zero ----
   if constexpr (kSplit) {
     constexpr int kVals = MB * 32;               // values per lane
     const size_t per_split = (size_t)NW * 64 * kVals;
@@ -816,7 +817,7 @@ __global__ __launch_bounds__(kWaves * 64) void awq_gemm_sm_kernel(
 }
 
 // RAG_AWQ_SM_NB / RAG_AWQ_SM_SPLITS (read at each call) fix the small-batch
-// column blocks per workgroup (2, 4 or 8, at most 8 / row blocks) and the split of the groups: a
+// column blocks per workgroup (1, 2, 4 or 8) and the least split of the groups: a
 // testing and tuning knob (any choice computes the same sums; only split
 // counts change the fp32 addition order).
 static int env_int(const char* name) {
@@ -824,9 +825,9 @@ static int env_int(const char* name) {
   return (e != nullptr && e[0] != 0) ? std::atoi(e) : 0;
 }
 
-// The tiles of awq_gemm_md_kernel and what they cost: kRes workgroups fit a CU
-// (registers); one group step takes kStep us with one of them resident and
-// kStep + (n - 1) kMore with n.
+// The tiles of awq_gemm_md_kernel and what they cost: `res` workgroups fit a CU
+// (registers); one group step takes `step` us with one of them resident and
+// step + (n - 1) more with n.
 struct MdTile {
   int mb, nw, res;
   double step, more;
@@ -836,10 +837,9 @@ static constexpr MdTile kMdTiles[] = {{1, 4, 3, 0.84, 0.47}, {2, 4, 2, 1.13, 0.7
                                       {5, 4, 1, 2.66, 0},    {4, 8, 1, 3.35, 0}};
 
 // Estimated time (us) of a launch: the busiest CU's n workgroups run in batches
-// of kRes.  A split adds the partials' trip (written once, read once by the
-// merging workgroups) and the merge's round trips.  Constants fitted to 1,900
-// timings (M 33-4096, the 7B layers and generic shapes): 8% rms off, and the
-// choice is on average 2% slower than the best of all (tile, split) pairs.
+// of `res`.  A split adds the partials' trip (written once, read once by the
+// merging workgroups) and the merge's round trips.  Constants fitted to timings
+// of every tile and split (M 33-4096, the 7B layers and generic shapes).
 static double awq_md_cost(const MdTile& c, int64_t tiles, int splits, int groups_per_split,
                           int64_t mn) {
   const int64_t n = (tiles * splits + kAwqCus - 1) / kAwqCus;      // on the busiest CU

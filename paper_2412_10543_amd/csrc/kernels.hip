@@ -9,7 +9,6 @@
 #include <algorithm>
 #include <climits>
 #include <cstdlib>
-#include <type_traits>
 
 #include "common.h"
 #include "decode_unit.h"
@@ -388,7 +387,7 @@ constexpr float kBalShort = D == 64 ? 45.f : 32.f;
 // busiest CU has with whole rows, one workgroup each, than with an even cut.
 // Fitted to 470 timed batches of 256-2000 pairs (32 to 9000 keys a row, ten head
 // shapes): within 0.3% of the better of plan and whole rows on average, where
-// always a plan is up to 1.4 times slower than whole rows (128 rows x 1200-1500
+// always a plan was up to 1.4 times slower than whole rows (128 rows x 1200-1500
 // keys, 2 kv heads: 33.4 us whole, 46.3 cut) and whole rows always up to 2.8
 // times than a plan (32 x 100-200 keys and one of 4000, 8 kv heads: 44.0 whole,
 // 15.9 cut).  40 x 2k-8k: 176 whole, 128 cut.
@@ -577,22 +576,31 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
   }
 }
 
-// Waves per SIMD of a kernel that may leave rows whole: those of the kernel that
-// always does (paged_decode_kernel; with one fewer 250 rows x 100-200 keys took
-// 39.9 us against 33.5, now 34.5).
-template <int D, bool kAppend, bool kFull>
-constexpr int bal_wgs() {
-  return kFull ? (D == 64 ? 3 : 2) + (kAppend ? 0 : 1) : 2;
+// Fewer (row, kv head) pairs than CUs: up to 64 rows, and up to kBalMaxRows.
+template <int D, bool kAppend>
+__global__ __launch_bounds__(kDecThreads, 2) void paged_decode_balanced_kernel(PagedKernelArgs a) {
+  __shared__ __attribute__((aligned(16))) bf16_t lds[DecLds<D>::kBytes / 2];
+  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, 1, false>(
+      a, blockIdx.x, a.hq / a.hkv, (size_t)a.hkv * 16 * D, lds, nullptr);
 }
 
-// kChunks: 1 up to 64 rows, kBalMaxChunks up to kBalMaxRows.  kFull: as many
-// (row, kv head) pairs as CUs, or more.
-template <int D, bool kAppend, int kChunks, bool kFull>
-__global__ __launch_bounds__(kDecThreads, (bal_wgs<D, kAppend, kFull>())) void
-paged_decode_balanced_kernel(PagedKernelArgs a) {
+template <int D, bool kAppend>
+__global__ __launch_bounds__(kDecThreads, 2) void paged_decode_balanced_rows_kernel(PagedKernelArgs a) {
   __shared__ __attribute__((aligned(16))) bf16_t lds[DecLds<D>::kBytes / 2];
-  __shared__ int keys[kFull ? kChunks * kWave : 1];
-  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, kChunks, kFull>(
+  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, kBalMaxChunks, false>(
+      a, blockIdx.x, a.hq / a.hkv, (size_t)a.hkv * 16 * D, lds, nullptr);
+}
+
+// As many pairs as CUs, or more; kChunks: 1 up to 64 rows, kBalMaxChunks up to
+// kBalMaxRows.  As many waves a SIMD as paged_decode_kernel, which leaves every
+// row whole (with one fewer 250 rows x 100-200 keys took 39.9 us against 33.5,
+// now 33.9).
+template <int D, bool kAppend, int kChunks>
+__global__ __launch_bounds__(kDecThreads, (D == 64 ? 3 : 2) + (kAppend ? 0 : 1)) void
+paged_decode_full_kernel(PagedKernelArgs a) {
+  __shared__ __attribute__((aligned(16))) bf16_t lds[DecLds<D>::kBytes / 2];
+  __shared__ int keys[kChunks * kWave];
+  decode_block_balanced<D, kDecPages, kDecWaves, kAppend, kChunks, true>(
       a, blockIdx.x, a.hq / a.hkv, (size_t)a.hkv * 16 * D, lds, keys);
 }
 
@@ -727,26 +735,28 @@ static hipError_t launch_paged_d(const PagedArgs& a, hipStream_t stream) {
       hipLaunchKernelGGL(mixed_kernel<D>, dim3((unsigned)grid), dim3(64 * kPfWavesDense), 0,
                          stream, k);
     else if (k.bal_units > 0) {
+      const bool full = (int64_t)a.num_decode * a.hkv >= kDecUnits, append = a.k_new != nullptr;
       // Up to four workgroups a CU: one fewer resident than the non-appending
       // kernels' registers allow, so that the last ones go where there is room
       // (36 rows x 157-1256 keys, 16 kv heads: 42 us with two a CU, 49 with three).
       constexpr int kSpareLds = D == 128 ? 18 << 10 : 21 << 10;
-      auto go = [&](auto append, auto chunks, auto full) {
-        hipLaunchKernelGGL((paged_decode_balanced_kernel<D, append.value, chunks.value,
-                                                         full.value>),
-                           dim3((unsigned)grid), dim3(kDecThreads),
-                           full.value && !append.value && grid <= 4 * kDecUnits ? kSpareLds : 0,
-                           stream, k);
+      const int spare = full && !append && grid <= 4 * kDecUnits ? kSpareLds : 0;
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kDecThreads), spare, stream, k);
       };
-      auto rows = [&](auto append, auto chunks) {
-        (int64_t)a.num_decode * a.hkv >= kDecUnits ? go(append, chunks, std::true_type())
-                                                   : go(append, chunks, std::false_type());
-      };
-      auto appending = [&](auto append) {
-        a.num_decode <= kWave ? rows(append, std::integral_constant<int, 1>())
-                              : rows(append, std::integral_constant<int, kBalMaxChunks>());
-      };
-      a.k_new != nullptr ? appending(std::true_type()) : appending(std::false_type());
+      const bool one = a.num_decode <= kWave;
+      if (full && append)
+        one ? go(paged_decode_full_kernel<D, true, 1>)
+            : go(paged_decode_full_kernel<D, true, kBalMaxChunks>);
+      else if (full)
+        one ? go(paged_decode_full_kernel<D, false, 1>)
+            : go(paged_decode_full_kernel<D, false, kBalMaxChunks>);
+      else if (append)
+        one ? go(paged_decode_balanced_kernel<D, true>)
+            : go(paged_decode_balanced_rows_kernel<D, true>);
+      else
+        one ? go(paged_decode_balanced_kernel<D, false>)
+            : go(paged_decode_balanced_rows_kernel<D, false>);
     }
     else if (a.k_new != nullptr)
       hipLaunchKernelGGL((paged_decode_kernel<D, true>), dim3((unsigned)grid), dim3(kDecThreads),
