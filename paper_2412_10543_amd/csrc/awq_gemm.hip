@@ -137,8 +137,9 @@ __device__ __forceinline__ ColScale col_scale(uint32_t sb, uint32_t z) {
 // zero scale turns the column's operands to zero (mask and magic 0) and leaves
 // c as it was.
 //
-// What bounds it.  The matrix cores with 128-row tiles (64% busy at 8192 rows:
-// 72 MFMAs a wave and group beside 340 vector instructions, 44 LDS reads);
+// What bounds it.  The matrix cores with 128-row tiles (hardware counters: busy
+// 64-70% of the cycles at 8192 rows, 38% with gate_up's 160-row tiles at 320: 72
+// MFMAs a wave and group beside 340 vector instructions, 44 LDS reads);
 // vector issue with the low tiles, where a converted code word serves fewer row
 // blocks; round trips (first loads, split merge) on small grids.  So each k-step
 // issues one MFMA, then a share of the next step's conversions, LDS reads,
