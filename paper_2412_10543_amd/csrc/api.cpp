@@ -163,7 +163,7 @@ WsLayout workspace_layout(int32_t num_decode, int32_t hq, int32_t d, int32_t spl
   if (splits <= 1 || num_decode <= 0) return w;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t rows = (size_t)num_decode * hq * splits;
-  w.o_off = (size_t)rag::kDecCounters * sizeof(int32_t);
+  w.o_off = rag::kDecCounterBytes;
   w.lse_off = w.o_off + up(rows * d * sizeof(float));
   w.bytes = w.lse_off + up(rows * sizeof(float));
   return w;

@@ -225,6 +225,9 @@ constexpr int kDecMaxSplits = 64;          // pieces of a row that a merge takes
 // were its size the call's own, a call of more rows would find partials where
 // it counts.
 constexpr int kDecCounters = 65536;
+// Their bytes in a workspace, and 512 more: partials at a multiple of 256 KiB cost
+// the merge 0.5% (16 rows of 2.6k-10.3k keys 58.8 us against 58.4).
+constexpr size_t kDecCounterBytes = kDecCounters * sizeof(int) + 512;
 constexpr int kDecUnits = 256;             // decode units aimed at, about one per CU
 constexpr int kDecMinPages = 16;           // fewest pages a balanced decode unit is cut for
 // Balanced decode: how far above the mean load (in pages) the largest whole

@@ -38,6 +38,17 @@ struct DecodeOut {
   int sp, n_sp, num_splits;
 };
 
+// The thread's index in the workgroup.  kLoop (units one after another in a loop
+// of a kernel with no registers to spare): formed anew each time, so that nothing
+// that follows from it is kept over the loop.
+template <bool kLoop>
+__device__ __forceinline__ unsigned unit_thread() {
+  if constexpr (!kLoop) return threadIdx.x;
+  unsigned t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t & (kDecThreads - 1);
+}
+
 // Per wave: attend the wave's steps of the page range.  Leaves, per lane
 // (head l16, lane group gq), the unnormalised O^T accumulators, the head's
 // sum of weights l (already reduced over the lane groups) and the reference
@@ -47,19 +58,18 @@ struct DecodeOut {
 // k_new and v_new (this kv head's rows) rather than the cache: the lanes that
 // would load that slot read them there instead (the cache slot is written in
 // the same launch, see decode_unit).
-template <int D, int NP, bool kAppend = false>
+template <int D, int NP, bool kAppend = false, bool kLoop = false>
 __device__ __forceinline__ void decode_wave(
-    int tid, bool mask, const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
+    bool mask, const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
     const bf16_t* __restrict__ vc, size_t block_stride, const int32_t* __restrict__ table,
     int kv_len, int group, int p_first, int p_end, int p_stride, float scale,
-    bf16_t* __restrict__ vt,
-    f32x4 (&oacc)[D / 16], float& m_used, float& l, const bf16_t* __restrict__ k_new = nullptr,
-    const bf16_t* __restrict__ v_new = nullptr) {
+    bf16_t* __restrict__ vt, f32x4 (&oacc)[D / 16], float& m_used, float& l,
+    const bf16_t* __restrict__ k_new = nullptr, const bf16_t* __restrict__ v_new = nullptr) {
   static_assert(NP % 2 == 0, "pages are consumed in pairs (32 keys per MFMA)");
   using L = DecLds<D, NP>;
   constexpr int kKs = D / 32;   // k-steps over d for S^T
   constexpr int kDt = D / 16;   // 16-row d tiles of O^T
-  const int lane = tid & 63;
+  const int lane = unit_thread<kLoop>() & 63;
   const int l16 = lane & 15, gq = lane >> 4;
 
   // Q^T fragments: lane holds head l16, d = 32*ks + 8*gq .. +8.  Lanes past the
@@ -227,11 +237,11 @@ __device__ __forceinline__ void decode_wave(
 // round trips to the coherence point (2.4 us before, 1.2 now at two splits),
 // and most rows have at most 8 splits.  (The mixed launch's eight-wave units
 // keep 16: 1714 us against 1735 with 8 on 256 rows and four pieces.)
-template <int D, int W>
-__device__ __forceinline__ void merge_splits(int tid, const DecodeOut& out, int group) {
+template <int D, int W, bool kLoop = false>
+__device__ __forceinline__ void merge_splits(const DecodeOut& out, int group) {
   constexpr int kPer = D / 64;                 // 2 (D = 128) or 1 (D = 64)
   constexpr int kBatch = W > 4 ? 16 : 8;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = unit_thread<kLoop>() & 63, wave = unit_thread<kLoop>() >> 6;
   for (int h = wave; h < group; h += W) {
     const float* pl = out.part_lse + (size_t)h * out.num_splits;
     const float* po = out.part_o + (size_t)h * out.num_splits * D + lane * kPer;
@@ -280,17 +290,17 @@ constexpr int dec_merge_bytes() {
   return (W * 16 * D + 2 * W * 16 + 1) * 4;
 }
 
-// The whole unit (tid: the thread's index in the workgroup): the W waves cover
-// the page range [p_begin, p_end) in interleaved steps of NP pages, merge
-// through LDS and write either the final rows (n_sp == 1) or this split's
-// partial rows; the last split of the row to arrive then merges all partials.
+// The whole unit: the workgroup's W waves cover the page range
+// [p_begin, p_end) in interleaved steps of NP pages, merge through LDS and
+// write either the final rows (n_sp == 1) or this split's partial rows; the
+// last split of the row to arrive then merges all partials.
 //
 // kAppend: the unit whose range holds the last page also stores the new
 // token's K and V rows (k_new, v_new) into its cache slot, key kv_len - 1 of
 // the block table.  No unit of this launch reads that slot from the cache.
-template <int D, int NP, int W, bool kAppend = false>
+template <int D, int NP, int W, bool kAppend = false, bool kLoop = false>
 __device__ __forceinline__ void decode_unit(
-    int tid, const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
     const bf16_t* __restrict__ vc, size_t block_stride, const int32_t* __restrict__ table,
     int kv_len, int group, int p_begin, int p_end, float scale, const DecodeOut& out,
     bf16_t* __restrict__ lds,
@@ -298,7 +308,7 @@ __device__ __forceinline__ void decode_unit(
   using L = DecLds<D, NP, W>;
   static_assert(dec_merge_bytes<D, W>() <= L::kBytes, "merge area must fit in the V slices");
   constexpr int kDt = D / 16;
-  const int wave = tid >> 6, lane = tid & 63;
+  const int wave = unit_thread<kLoop>() >> 6, lane = unit_thread<kLoop>() & 63;
   const int l16 = lane & 15, gq = lane >> 4;
 
   // The new token's rows and their slot are requested before the pages and
@@ -313,9 +323,9 @@ __device__ __forceinline__ void decode_unit(
   }
   f32x4 oacc[kDt];
   float m_used, l;
-  decode_wave<D, NP, kAppend>(tid, W <= 4, q, kc, vc, block_stride, table, kv_len, group,
-                              p_begin + wave * NP, p_end, W * NP, scale,
-                              lds + wave * L::kElemsWave, oacc, m_used, l, k_new, v_new);
+  decode_wave<D, NP, kAppend, kLoop>(W <= 4, q, kc, vc, block_stride, table, kv_len, group,
+                                     p_begin + wave * NP, p_end, W * NP, scale,
+                                     lds + wave * L::kElemsWave, oacc, m_used, l, k_new, v_new);
 
   if (store_new) {
     asm volatile("" : "+v"(new_page));   // (no arithmetic on it, hence no wait, before here)
@@ -385,12 +395,12 @@ __device__ __forceinline__ void decode_unit(
   wait_all_memory();
   __syncthreads();
   int* flag = reinterpret_cast<int*>(ml + W * 16);
-  if (tid == 0)
+  if (threadIdx.x == 0)
     *flag = __hip_atomic_fetch_add(out.arrival, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if (*flag != out.n_sp - 1) return;
-  merge_splits<D, W>(tid, out, group);
-  if (tid == 0)
+  merge_splits<D, W, kLoop>(out, group);
+  if (threadIdx.x == 0)
     __hip_atomic_store(out.arrival, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 

@@ -290,8 +290,8 @@ struct PagedKernelArgs {
 
 // One piece of a decode row: pages [p_begin, p_end) of (row s, kv head kvh),
 // split sp of n_sp, on W waves taking NP pages a step.
-template <int D, int NP, int W, bool kAppend = false>
-__device__ __forceinline__ void decode_piece(int tid, const PagedKernelArgs& a, int group,
+template <int D, int NP, int W, bool kAppend = false, bool kLoop = false>
+__device__ __forceinline__ void decode_piece(const PagedKernelArgs& a, int group,
                                              size_t block_stride, int s, int kvh, int kv_len,
                                              int p_begin, int p_end, int sp, int n_sp,
                                              bf16_t* lds) {
@@ -306,11 +306,10 @@ __device__ __forceinline__ void decode_piece(int tid, const PagedKernelArgs& a, 
   out.n_sp = n_sp;
   out.num_splits = a.slots;
   const size_t nrow = ((size_t)s * a.hkv + kvh) * D;
-  decode_unit<D, NP, W, kAppend>(tid, a.q + head * D, a.kc + (size_t)kvh * 16 * D,
-                                 a.vc + (size_t)kvh * 16 * D, block_stride,
-                                 a.tables + (size_t)s * a.max_blocks, kv_len, group, p_begin,
-                                 p_end, a.scale, out, lds, kAppend ? a.k_new + nrow : nullptr,
-                                 kAppend ? a.v_new + nrow : nullptr);
+  decode_unit<D, NP, W, kAppend, kLoop>(
+      a.q + head * D, a.kc + (size_t)kvh * 16 * D, a.vc + (size_t)kvh * 16 * D, block_stride,
+      a.tables + (size_t)s * a.max_blocks, kv_len, group, p_begin, p_end, a.scale, out, lds,
+      kAppend ? a.k_new + nrow : nullptr, kAppend ? a.v_new + nrow : nullptr);
 }
 
 // Decode unit u with fixed page ranges (see above), on W waves.
@@ -328,8 +327,8 @@ __device__ __forceinline__ void decode_block(const PagedKernelArgs& a, int u, in
   if (sp >= n_sp && sp > 0) return;
   const int p_begin = sp * a.pps;
   const int p_end = min(n_pages, p_begin + a.pps);
-  decode_piece<D, NP, W, kAppend>(threadIdx.x, a, group, block_stride, s, kvh, kv_len, p_begin,
-                                  p_end, sp, n_sp, lds);
+  decode_piece<D, NP, W, kAppend>(a, group, block_stride, s, kvh, kv_len, p_begin, p_end, sp,
+                                  n_sp, lds);
 }
 
 // Balanced decode units: a pure decode batch is cut into units from the rows'
@@ -445,8 +444,8 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
     // rows, short as a rule, took 0.4-0.7 us longer)
     if (k >= S) return;
     const int kls = min(a.kv_lens[k], cap);
-    decode_piece<D, NP, W, kAppend>(threadIdx.x, a, group, block_stride, k, kvh, kls, 0,
-                                    (kls + 15) >> 4, 0, 1, lds);
+    decode_piece<D, NP, W, kAppend>(a, group, block_stride, k, kvh, kls, 0, (kls + 15) >> 4, 0, 1,
+                                    lds);
     return;
   }
   // Pages per unit below which the longest row could have more pieces than the
@@ -541,18 +540,15 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
   }
   // one call site of decode_piece: the plans' code stays one copy of the unit
   if constexpr (kFull) {
-    // What is kept per lane, or formed from the thread's index, would sit in
-    // registers through the page loop of a kernel that has none to spare.
+    // (what is kept per lane would sit in registers through the page loop)
     int gs = row(st, s), ps = row(pg, s), kls = row(kl, s);
     int ufs = row(uf, s), uns = row(un, s);
     for (bool first = true;; first = false) {
       if (ps > 0) {
         if (!first) __syncthreads();         // LDS of the previous piece fully read
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        decode_piece<D, NP, W, kAppend>(tid & (kDecThreads - 1), a, group, block_stride, s, kvh,
-                                        kls, max(lo, gs) - gs, min(hi, gs + ps) - gs, k - ufs, uns,
-                                        lds);
+        decode_piece<D, NP, W, kAppend, true>(a, group, block_stride, s, kvh, kls,
+                                              max(lo, gs) - gs, min(hi, gs + ps) - gs, k - ufs,
+                                              uns, lds);
       }
       gs += ps;
       if (++s >= S || gs >= hi) break;
@@ -567,7 +563,7 @@ __device__ __forceinline__ void decode_block_balanced(const PagedKernelArgs& a, 
       if (gs >= hi) break;
       if (ps > 0) {
         if (!first) __syncthreads();         // LDS of the previous piece fully read
-        decode_piece<D, NP, W, kAppend>(threadIdx.x, a, group, block_stride, s, kvh, row(kl, s),
+        decode_piece<D, NP, W, kAppend>(a, group, block_stride, s, kvh, row(kl, s),
                                         max(lo, gs) - gs, min(hi, gs + ps) - gs, k - row(uf, s),
                                         row(un, s), lds);
       }
